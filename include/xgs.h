@@ -170,10 +170,13 @@ xgs_status xgs_project_posed(const xgs_gaussians* g, const xgs_camera* cam, cons
                              xgs_projected* out, xgs_stream_t stream);
 
 /* ------------------------------------------------------- a2: tile sort
- * Binning and depth sort ("depth-sorted Gaussians", Sec. 3.1): exclusive scan
- * of tiles_touched, emission of one key per (tile, Gaussian) in Gaussian
- * order, stable LSD radix sort over the 32 + ceil(log2(tiles)) key bits, and
- * per-tile ranges.  Reads p->tile_rect, p->tiles_touched and the depth of
+ * Binning and depth sort ("depth-sorted Gaussians", Sec. 3.1): one key per
+ * (tile, Gaussian), ordered by tile, then depth, then Gaussian index, and
+ * per-tile ranges.  Up to 16384 tiles and 8192 instances of capacity per tile
+ * the instances are counted per tile, dropped into their tiles' segments and
+ * sorted there; beyond, and with a workspace too small for that, they are
+ * emitted in Gaussian order and go through a stable LSD radix sort.  Both
+ * give the same arrays.  Reads p->tile_rect, p->tiles_touched and the depth of
  * p->splat.  ws must hold xgs_tile_sort_workspace(n, max_instances, tiles)
  * bytes, 256-byte aligned. */
 size_t xgs_tile_sort_workspace(int64_t n, int64_t max_instances, int32_t num_tiles);

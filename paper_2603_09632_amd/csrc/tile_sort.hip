@@ -1,11 +1,16 @@
 // a2: binning of projected splats into 16x16 tiles and per-tile depth sort.
+// Grids of up to 16,384 tiles take the binning form (tile_bins.hip); this file
+// holds the entry points and the radix form.
 // Keys are (tile_id << 32) | bits(depth): camera depths are positive, and
 // positive IEEE binary32 values order like their bit patterns.  Keys are
 // emitted in Gaussian order and sorted with a stable LSD radix sort, so equal
 // keys keep ascending Gaussian index.
+#include <algorithm>
 #include <mutex>
 
+#include "order.h"
 #include "sort.h"
+#include "tile_bins.h"
 
 namespace xgs {
 
@@ -187,97 +192,11 @@ static int tile_bits(int64_t tiles) {
     return b;
 }
 
-// Tile processing order for the compositing kernels: tiles by descending
-// list length (in buckets of 16 instances, capped at 255 buckets), ties by
-// tile index, so the longest lists are dispatched first and the short ones
-// fill the machine behind them.  One workgroup runs a stable counting sort on
-// the key 255 - bucket: each of the 16 wavefronts owns a contiguous range of
-// tile ids and walks it 64 tiles at a time; lanes with equal keys find each
-// other with eight ballots (one per key bit), so a lane's rank among equal
-// keys is a popcount and no atomics are needed.  The result is fully
-// determined.  Up to kOrderMax tiles; beyond that the order is the identity.
-constexpr int kOrderMax = 16384;
-constexpr int kOrderWaves = 16;
-
-// For a lane in `valid`: the lanes of `valid` whose key equals its own.
-__device__ __forceinline__ uint64_t same_key_lanes(uint32_t key, uint64_t valid) {
-    // one key across the valid lanes (runs of empty tiles): no bit ballots
-    const uint32_t k0 = __builtin_amdgcn_readlane(key, valid ? __builtin_ctzll(valid) : 0);
-    if (__ballot(((valid >> __lane_id()) & 1ull) && key != k0) == 0ull) return valid;
-    uint64_t m = valid;
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-        const bool on = (key >> bit) & 1u;
-        const uint64_t bl = __ballot(on);
-        m &= on ? bl : ~bl;
-    }
-    return m;
-}
-
-__global__ void __launch_bounds__(1024) tile_order_kernel(const uint32_t* __restrict__ ranges, int T,
-                                                         uint32_t* __restrict__ order) {
-    constexpr int kIters = kOrderMax / (kOrderWaves * 64);  // 64-tile steps per wavefront
-    __shared__ uint32_t cnt[kOrderWaves][256];  // per wave and key: count, then next output slot
-    __shared__ uint32_t ws[4];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    for (int i = t; i < kOrderWaves * 256; i += 1024) (&cnt[0][0])[i] = 0;
-    const int per = (T + kOrderWaves - 1) / kOrderWaves;
-    const int lo = min(T, w * per), hi = min(T, lo + per);
-    const uint64_t lt = (1ull << lane) - 1ull;
-    // every key of the wavefront's range is loaded up front (in-bounds
-    // clamped reads past the range, ignored): a load per 64-tile step would
-    // put a full memory latency in front of each step, twice
-    uint32_t key[kIters];
-#pragma unroll
-    for (int it = 0; it < kIters; ++it) {
-        const int i = lo + it * 64 + lane;
-        const int ic = min(i, T - 1);
-        const uint32_t len = ranges[2 * ic + 1] - ranges[2 * ic];
-        key[it] = i < hi ? 255u - min(len >> 4, 255u) : 0u;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < kIters; ++it) {
-        if (lo + it * 64 >= hi) break;  // uniform across the wavefront
-        const bool ok = lo + it * 64 + lane < hi;
-        const uint64_t m = same_key_lanes(key[it], __ballot(ok));
-        if (ok && (m & lt) == 0) cnt[w][key[it]] += (uint32_t)__popcll(m);
-    }
-    __syncthreads();
-    // exclusive prefix over keys of the totals (four wavefront scans), then
-    // over waves within a key
-    uint32_t s = 0, incl = 0;
-    if (t < 256) {
-#pragma unroll
-        for (int v = 0; v < kOrderWaves; ++v) s += cnt[v][t];
-        incl = wave_incl_scan(s, lane);
-        if (lane == 63) ws[w] = incl;
-    }
-    __syncthreads();
-    if (t < 256) {
-        uint32_t pre = incl - s;  // tiles with a smaller key
-#pragma unroll
-        for (int k = 0; k < 4; ++k) pre += k < w ? ws[k] : 0u;
-#pragma unroll
-        for (int v = 0; v < kOrderWaves; ++v) {
-            const uint32_t c = cnt[v][t];
-            cnt[v][t] = pre;
-            pre += c;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < kIters; ++it) {
-        if (lo + it * 64 >= hi) break;
-        const int i = lo + it * 64 + lane;
-        const bool ok = i < hi;
-        const uint64_t m = same_key_lanes(key[it], __ballot(ok));
-        const uint32_t base = ok ? cnt[w][key[it]] : 0u;
-        const uint32_t pos = base + (uint32_t)__popcll(m & lt);
-        if (ok && pos < (uint32_t)T) order[pos] = (uint32_t)i;
-        // every lane has read its base before the group leader advances it
-        if (ok && (m & lt) == 0) cnt[w][key[it]] = base + (uint32_t)__popcll(m);
-    }
+// The order table from the ranges (one workgroup).
+__global__ void __launch_bounds__(kOrderThreads) tile_order_kernel(const uint32_t* __restrict__ ranges, int T,
+                                                                  uint32_t* __restrict__ order) {
+    __shared__ uint32_t lds[kOrderLdsBytes / sizeof(uint32_t)];
+    order_tiles(T, order, lds, [&](int i) { return ranges[2 * i + 1] - ranges[2 * i]; });
 }
 
 __global__ void __launch_bounds__(256) tile_order_identity_kernel(int64_t T, uint32_t* __restrict__ order) {
@@ -290,10 +209,10 @@ __global__ void __launch_bounds__(256) tile_order_identity_kernel(int64_t T, uin
 using namespace xgs;
 
 extern "C" size_t xgs_tile_sort_workspace(int64_t n, int64_t max_instances, int32_t num_tiles) {
-    (void)num_tiles;
-    size_t bytes = 0;
+    size_t bytes = 0, bins = 0;
     carve_sort(nullptr, n < 0 ? 0 : n, max_instances < 0 ? 0 : max_instances, &bytes);
-    return bytes;
+    if (bins_apply(n, max_instances, num_tiles)) carve_bins(nullptr, n, max_instances, num_tiles, &bins);
+    return std::max(bytes, bins);
 }
 
 extern "C" xgs_status xgs_tile_sort(const xgs_projected* p, const xgs_camera* cam, int64_t n,
@@ -318,6 +237,13 @@ extern "C" xgs_status xgs_tile_sort(const xgs_projected* p, const xgs_camera* ca
     Grid g = grid_of(*cam);
     int64_t tiles = (int64_t)g.tx * g.ty;
     const int64_t cap = b->max_instances;
+    // Binning by tile for up to 16,384 tiles and 8,192 instances of capacity
+    // per tile; a workspace that holds the radix form only keeps the radix form.
+    if (bins_apply(n, cap, tiles)) {
+        size_t bytes = 0;
+        const BinWs bw = carve_bins(ws, n, cap, tiles, &bytes);
+        if (ws_bytes >= bytes) return bin_tile_sort(p, n, g.tx, tiles, bw, b, st);
+    }
     int bits = 32 + tile_bits(tiles);
     bool even = radix_passes(bits, cap) % 2 == 0;
     uint64_t* k0 = even ? b->keys : w.keys_alt;
@@ -350,7 +276,7 @@ extern "C" xgs_status xgs_tile_sort(const xgs_projected* p, const xgs_camera* ca
     if ((s = segment_ranges(b->keys, b->num_instances, cap, 32, b->ranges, st))) return s;
     if (b->tile_order && tiles > 0) {
         if (tiles <= kOrderMax)
-            hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(1024), 0, st, b->ranges, (int)tiles, b->tile_order);
+            hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(kOrderThreads), 0, st, b->ranges, (int)tiles, b->tile_order);
         else
             hipLaunchKernelGGL(tile_order_identity_kernel, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, st,
                                tiles, b->tile_order);
