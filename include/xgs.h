@@ -229,8 +229,8 @@ xgs_status xgs_render_fwd(const xgs_gaussians* g, const xgs_projected* p, const 
 enum { XGS_BWD_ALL = 0, XGS_BWD_FEATURES_ONLY = 1, XGS_BWD_PREZEROED = 2 };
 size_t xgs_render_bwd_workspace(int64_t n);
 /* The zeroing that xgs_render_bwd does first, as a call of its own: the
- * accumulated gradients (features; with XGS_BWD_ALL also colours and
- * opacity) and the workspace's per-Gaussian rows.  A caller can issue it
+ * accumulated gradients (features) and, with XGS_BWD_ALL, the workspace's
+ * per-Gaussian rows, from which the second kernel writes the others.  A caller can issue it
  * earlier, on another stream (overlapping the forward pass), and then call
  * xgs_render_bwd with flags | XGS_BWD_PREZEROED on the same grads and ws,
  * which then skips its own zeroing; the caller orders the two (an event). */

@@ -6,64 +6,99 @@
 // starting from final_T, so nothing per (pixel, Gaussian) is stored by the
 // forward pass.  With S_k = sum_{j>k} a_j T_j (g . c_j), the derivative of
 // Eq. (rendering) is dL/da_k = T_k (g . c_k) - S_k / (1 - a_k).  The per-pixel
-// contributions of one Gaussian are summed over the wavefront by a
-// reduce-scatter (each exchange halves the number of live values per lane), so
-// one atomic instruction per Gaussian and wave carries all of its sums.
+// contributions of a Gaussian are summed over the wavefront by reduce-scatters
+// (each exchange halves the number of live values per lane) before one atomic
+// add per value.
 //
 // Gaussian pass: gradients of (mean2d, conic, depth) are carried back through
 // conic = Sigma'^-1, Sigma' = J Sigma_cam J^T + 0.3 I, Sigma_cam = Rv Sigma Rv^T,
 // Sigma = (R S)(R S)^T, p = Rv mu + t (App. A).
+#include <algorithm>
+#include <type_traits>
+
 #include "render_common.h"
 #include "sort.h"
 #include "wave.h"
 
 namespace xgs {
 
-// Geometry workspace row per Gaussian (8 floats).
-enum { GW_MX = 0, GW_MY = 1, GW_A = 2, GW_B = 3, GW_C = 4, GW_DEPTH = 5, GW_STRIDE = 8 };
+// Workspace row per Gaussian (64 bytes, 10 floats used): with h = a_k dL/da_k
+// (0 where alpha is clamped) and (dx, dy) from the splat's mean to the pixel,
+// dL/dmean2d, the sums of h dx^2, h dx dy, h dy^2 and h over the pixels (dL/dconic
+// and dL/dopacity but for constants and the opacity), then dL/ddepth and
+// dL/dcolour.  One row of one half cache line, because the atomics cost by the
+// requests that they make, not by their values: with the sums in rows of 32
+// bytes, colours and depth added on their own and features 16 at a time (80
+// requests for a batch of 16 splats and 32 features) the call took 431 us on 1M
+// Gaussians at 1200 x 680; with this row and 32 features at a time, 373; with no
+// atomics at all, 350.
+enum { GW_MX = 0, GW_MY = 1, GW_XX = 2, GW_XY = 3, GW_YY = 4, GW_1 = 5, GW_DEPTH = 6, GW_COLOR = 7, GW_USED = 10,
+       GW_STRIDE = 16 };
 
+// What bounds it: the instructions of one wavefront's walk (about 1,000 vector
+// and 84 matrix instructions a batch of 16 splats, 2 wavefronts a SIMD at 32
+// features) and, where few lists are long, the longest list's walk.  The whole
+// call with 6 sums a pixel reduced two splats at a time and per-value atomics,
+// and as it is: 1M Gaussians, 1200 x 680, 32 features 622 -> 375 us; 300k, 640 x
+// 480, 16 features 173 -> 94; 123k on a 321 x 240 grid, 20 features 131 -> 78.
+// Measured and not taken: the two products interleaved with the walk of the
+// batch between them (486 against 440 us at that stage); three wavefronts a SIMD
+// instead of two at 16 features, and a higher issue priority for long lists (no
+// change).
+//
 // The walk runs back to front.  The tile list is read 64 entries at a time
 // (one per lane: list entry and splat record, the next 64 in flight), the
 // splats that can reach alpha >= 1/255 somewhere in the wavefront's quadrant
 // are appended to a ring in LDS (quad_hit; the others are skipped by all 64
 // pixels) and the walk takes the ring 16 at a time, with the channel rows of
-// the next batch in flight.  Per Gaussian each pixel recovers T_k, forms
-// w_k = a_k T_k and dL/da_k; the six geometric sums (opacity, conic A B C,
-// mean x y) are reduced over the wavefront at once (reduce-scatter, 6 values)
-// and added atomically.  The channel gradients dL/dc_k = sum_p w_k(p) g(p) of
-// the batch are one 16 x 64 x 48 product W^T G on v_mfma_f32_16x16x4_f32:
-// W goes through LDS, G (the wave's upstream gradients in operand layout) is
-// loaded once.
-template <int CS, bool GEO, bool EXACT>
-__global__ void __launch_bounds__(64) render_bwd_mfma_kernel(
+// the next batch in flight.
+//
+// A pixel takes the splats eight at a time: first the eight alphas, which do
+// not depend on each other (0 for a pair that does not contribute, which then
+// leaves T and S as they are without further selects), then the chain of T and
+// S.  With b = a / (1 - a): w = b T, h = b (T g.c - S), S += w g.c, T /= 1 - a.
+// The sums over the quadrant are formed in two steps.  Over the rows (lane
+// bits 3-5): h, h dy and h dy^2 of the eight splats, by a reduce-scatter that
+// halves the splats at each exchange, so that lanes 8 s .. 8 s + 7 end with
+// the column sums of splat s.  Over the columns: from those and the column's dx
+// the six values of the row (h, dL/dmean2d = sum of h (A dx + B dy, B dx + C dy),
+// h dx^2, h dx dy, h dy^2), whose reduce-scatter leaves one on each of six lanes.
+// The channel gradients dL/dc_k = sum_p w_k(p) g(p) of the batch are one
+// product W^T G on v_mfma_f32_16x16x4_f32 (features first, then
+// colour and depth), and
+// the batch's g.c another; g.c and then w go through one LDS array.
+// OFF: the type of a byte offset into the per-Gaussian rows: 32 bits where they
+// all fit (an address is then one scalar base and one register).
+template <typename OFF, typename T>
+__device__ __forceinline__ T* at_row(T* base, uint32_t row, int stride, int word) {
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte;
+    return reinterpret_cast<T*>(reinterpret_cast<byte*>(base) + ((OFF)row * (OFF)(4 * stride) + (OFF)(4 * word)));
+}
+
+template <int CS, bool GEO, bool EXACT, typename OFF>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 16 ? 3 : 1))) render_bwd_mfma_kernel(
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float4* __restrict__ splat, const float* __restrict__ colors,
     const float* __restrict__ features, int csem, TileGrid g, const float* __restrict__ d_out,
     const float* __restrict__ final_T, const int32_t* __restrict__ n_last,
-    float* __restrict__ d_colors, float* __restrict__ d_features, float* __restrict__ d_opacity,
-    float* __restrict__ geo) {
+    float* __restrict__ d_features, float* __restrict__ geo) {
     constexpr int CH = 4 + CS;
     constexpr int CHP = (CH + 3) / 4 * 4;           // LDS row stride (float4 rows)
-    constexpr int NT = (CH + 15) / 16;
-    constexpr int VG = 6;
-    __shared__ float wl[64 * 17];
+    constexpr int COLS = GEO ? CH : CS;             // columns of W^T G: features, then colour and depth
+    constexpr int NT = (COLS + 15) / 16;
+    constexpr int ROW = 20;                         // LDS row of a pixel: 16 splats, float4-aligned, banks spread
+    __shared__ __align__(16) float wl[64 * ROW];    // g.c of (pixel, splat), then its weight
     __shared__ Ring ring;
-    __shared__ __align__(16) float chl[16 * CHP];
-    __shared__ float sdl[GEO ? 64 * 17 : 1];
+    __shared__ __align__(16) float chl[GEO ? 16 * CHP : 4];
     const QuadPix P = quad_pixel(g);
     if (P.tile >= g.tiles) return;
     const QuadRect qr = quad_rect(g, P);
     const int lane = threadIdx.x;
-    int my_id = 0;
-    bool my_own = false;
-    if (GEO) rs_layout<2 * VG>(lane, &my_id, &my_own);
-    const int my_split = my_id / VG, my_v = my_id - VG * (my_id / VG);  // splat of the pair, sum
-    // the array and stride that this lane's sum goes to (lane-constant, so the
-    // walk adds without branching on the destination)
-    float* const g_base = my_v == 0 ? d_opacity
-                                    : geo + (my_v == 1 ? GW_A : my_v == 2 ? GW_B : my_v == 3 ? GW_C
-                                                        : my_v == 4 ? GW_MX : GW_MY);
-    const int g_stride = my_v == 0 ? 1 : GW_STRIDE;
+    // the sum that ends on this lane after the column reduce-scatter (ids: 0 h,
+    // 1 mean y, 2 h dy^2, 3 mean x, 4 h dx dy, 5 h dx^2), as its place in the row
+    const int id = 3 * ((lane >> 2) & 1) + ((lane & 1) ? 2 : (lane >> 1) & 1);
+    const bool my_own = (lane & 3) != 3;
+    const int my_word = id == 0 ? GW_1 : id == 1 ? GW_MY : id == 2 ? GW_YY : id == 3 ? GW_MX : id == 4 ? GW_XY : GW_XX;
     const size_t hw = (size_t)g.hs * g.ws;
     const int fstride = EXACT ? CS : csem;
     const int qx = P.n - (lane & 7), qy = P.m - (lane >> 3);  // quadrant origin
@@ -76,8 +111,9 @@ __global__ void __launch_bounds__(64) render_bwd_mfma_kernel(
         const bool in = m < g.hs && n < g.ws;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int c = 16 * nt + (lane & 15);
-            const bool use = in && c < CH && (GEO || c >= 4) && (EXACT || c < 4 + csem);
+            const int j = 16 * nt + (lane & 15);
+            const int c = j < CS ? 4 + j : j - CS;
+            const bool use = in && j < COLS && (EXACT || j >= CS || j < csem);
             bg[nt][kk] = use ? d_out[c * hw + (size_t)m * g.ws + n] : 0.f;
         }
     }
@@ -109,82 +145,113 @@ __global__ void __launch_bounds__(64) render_bwd_mfma_kernel(
     const uint32_t start = uniform(ranges[2 * P.tile]);
     const int top = (int)uniform((uint32_t)jmax);
 
-    // candidate registers: list entry and splat record of position cpos - 1 - lane
-    int cg = -1;
-    float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
-    auto fetch = [&](int pos) {
-        const int j = pos - 1 - lane;
-        cg = -1;
-        if (j >= 0) {
-            cg = (int)vals[start + (uint32_t)j];
+    if (top == 0) return;  // no pixel of the quadrant blended anything
+
+    // Candidate registers: the splat record c0, c1 and index cg of list
+    // position cpos - 1 - lane, and the index cn of the position 64 before it
+    // (so that a record's load never waits for its list entry).  Positions
+    // before the list's start read its first entry and are not pushed.
+    auto entry = [&](int pos) { return (int)vals[start + (uint32_t)max(pos - 1 - lane, 0)]; };
+    int cpos = top, head = 0, tail = 0;
+    bool padded = false;
+    int cg = entry(cpos), cn = entry(cpos - 64);
+    float4 c0 = splat[2 * (uint32_t)cg], c1 = splat[2 * (uint32_t)cg + 1];
+    // keeps at least two batches after `used` in the ring (or everything that is
+    // left); the slots written lie past the two batches being read
+    auto fill = [&](int used) {
+        while (tail - used < 32 && cpos > 0) {
+            const int pos = cpos - 1 - lane;
+            tail = ring_push(ring, tail, pos >= 0 && quad_hit(c0, c1, qr), c0, c1, cg, pos);
+            cpos -= 64;
+            cg = cn;
             c0 = splat[2 * (uint32_t)cg];
             c1 = splat[2 * (uint32_t)cg + 1];
+            cn = entry(cpos - 64);
+        }
+        if (cpos <= 0 && !padded) {
+            // sixteen slots that no pixel takes follow the last splat, so that
+            // the walk need not look at a batch's size
+            padded = true;
+            if (lane < 16) {
+                const int at = (tail + lane) & (kRing - 1);
+                ring.rec[at][0] = make_float4(0.f, 0.f, 0.f, 0.f);
+                ring.rec[at][1] = make_float4(0.f, 0.f, 0.f, __int_as_float(0x7FFFFFFF));
+                ring.gid[at] = cg;
+            }
         }
     };
-    int cpos = top, head = 0, tail = 0;
-    // keeps at least two batches in the ring (or everything that is left);
-    // the slots written lie past the two batches being read
-    auto fill = [&]() {
-        while (tail - head < 32 && cpos > 0) {
-            tail = ring_push(ring, tail, cg >= 0 && quad_hit(c0, c1, qr), c0, c1, cg, cpos - 1 - lane);
-            cpos -= 64;
-            fetch(cpos);
-        }
-    };
-    // Channel rows of a batch (only the S = C G^T product reads them): the
-    // colour and depth of splat lane / 4 (channel lane % 4) in one load, then
-    // the feature rows as 64 consecutive (splat, feature) pairs per load, so
-    // that every load reads one array and feature rows are read contiguously.
-    // Slots past the batch hold zeros.
-    constexpr int PERF = (16 * CS + 63) / 64;
+    // Channel rows of a batch (only the S = C G^T product reads them): lane
+    // 4 k + c takes splat k: colour c or the depth, and where the rows are whole
+    // groups of four features, groups c, c + 4, ... of its row.  (Vector loads of
+    // 4-byte alignment: a row may start anywhere.)  Other rows are read as 64
+    // consecutive (splat, feature) pairs per load.  Slots past the batch hold
+    // the index of some splat; nothing of them is used.
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr bool QUADS = EXACT && CS % 4 == 0;
+    constexpr int GRP = QUADS ? (CS + 15) / 16 : 0;
+    constexpr int PERF = QUADS ? 0 : (16 * CS + 63) / 64;
     constexpr int CSD = CS > 0 ? CS : 1;  // divisor (no feature loads when CS = 0)
-    float cv[GEO ? 1 + PERF : 1];
+    float cv[1 + PERF], cdepth = 0.f;
+    f4u cq[GRP > 0 ? GRP : 1];
     auto fetch_channels = [&](int base, int n) {
-        if constexpr (GEO) {
-            {
-                const int k = lane >> 2, c = lane & 3;
-                const int gk = k < n ? ring.gid[(base + k) & (kRing - 1)] : -1;
-                const uint32_t i = (uint32_t)(gk >= 0 ? gk : 0);
-                const float* src = c < 3 ? colors + 3 * (size_t)i + c
-                                         : reinterpret_cast<const float*>(splat) + 8 * (size_t)i + 6;  // depth
-                cv[0] = gk >= 0 ? *src : 0.f;
-            }
+        if (!GEO || n == 0) return;
+        const int k = lane >> 2, c = lane & 3;
+        const int at = (base + k) & (kRing - 1);
+        const uint32_t i = (uint32_t)ring.gid[at];
+        cdepth = ring.rec[at][1].z;
+        cv[0] = *at_row<OFF>(colors, i, 3, min(c, 2));
 #pragma unroll
-            for (int t = 1; t <= PERF; ++t) {
-                const int e = lane + 64 * (t - 1);
-                const int k = e / CSD, f = e - k * CSD;
-                const int gk = k < n ? ring.gid[(base + k) & (kRing - 1)] : -1;
-                cv[t] = (gk >= 0 && (EXACT || f < csem)) ? features[(size_t)gk * fstride + f] : 0.f;
-            }
+        for (int t = 0; t < GRP; ++t)
+            if (16 * t + 16 <= CS || 16 * t + 4 * c < CS)
+                cq[t] = *reinterpret_cast<const f4u*>(at_row<OFF>(features, i, CS, 16 * t + 4 * c));
+#pragma unroll
+        for (int t = 1; t <= PERF; ++t) {
+            const int e = lane + 64 * (t - 1);
+            const int ke = e / CSD, f = e - ke * CSD;
+            // past the sixteen splats the ring may hold no index yet
+            const uint32_t ie = (uint32_t)ring.gid[(base + min(ke, 15)) & (kRing - 1)];
+            cv[t] = *at_row<OFF>(features, ie, fstride, EXACT ? f : min(f, csem - 1));
         }
     };
     auto store_channels = [&]() {
         if constexpr (GEO) {
-            chl[(lane >> 2) * CHP + (lane & 3)] = cv[0];
+            float* const row = chl + (lane >> 2) * CHP;
+            row[lane & 3] = (lane & 3) < 3 ? cv[0] : cdepth;
+#pragma unroll
+            for (int t = 0; t < GRP; ++t)
+                if (16 * t + 16 <= CS || 16 * t + 4 * (lane & 3) < CS)
+                    *reinterpret_cast<f32x4_t*>(row + 4 + 16 * t + 4 * (lane & 3)) = cq[t];
 #pragma unroll
             for (int t = 1; t <= PERF; ++t) {
                 const int e = lane + 64 * (t - 1);
                 const int k = e / CSD, f = e - k * CSD;
-                if (k < 16) chl[k * CHP + 4 + f] = cv[t];
+                if (64 * t <= 16 * CS || k < 16) chl[k * CHP + 4 + f] = EXACT || f < csem ? cv[t] : 0.f;
             }
         }
     };
     if constexpr (GEO && CHP > CH) {  // padding columns, read as zeros by the product
         for (int i = lane; i < 16 * (CHP - CH); i += 64) chl[(i / (CHP - CH)) * CHP + CH + i % (CHP - CH)] = 0.f;
     }
-    fetch(top);
-    fill();
+    // A batch's memory operations are ordered so that nothing waits for an
+    // atomic's return: vector memory operations complete in order and the
+    // compiler cannot count conditional ones, so a wait for any load after an
+    // atomic would drain the atomics too.  Each round issues the loads of the
+    // next batch's channels first, waits for them after the walk, refills the
+    // ring (whose candidates were loaded a round before), and issues its atomics
+    // last: they have the next round's walk to complete.
+    fill(head);
     __syncthreads();
     int nb = min(16, tail - head);
     fetch_channels(head, nb);
+    store_channels();
     float S = 0.f;
     while (nb > 0) {
-        store_channels();
-        fill();
         __syncthreads();
+        const int nb2 = min(16, tail - head - nb);
+        fetch_channels(head + nb, nb2);
         if constexpr (GEO) {
             // S = C G^T on the matrix cores (A: splat lane % 16, channel 4 kc + lane / 16),
-            // stored as sdl[pixel][splat] for the walk
+            // stored as wl[pixel][splat] for the walk
             f32x4_t sacc[4];
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt) sacc[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -196,59 +263,65 @@ __global__ void __launch_bounds__(64) render_bwd_mfma_kernel(
             }
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sdl[(16 * nt + (lane & 15)) * 17 + 4 * (lane >> 4) + r] = sacc[nt][r];
+                *reinterpret_cast<f32x4_t*>(&wl[(16 * nt + (lane & 15)) * ROW + 4 * (lane >> 4)]) = sacc[nt];
         }
-        const int nb2 = min(16, tail - head - nb);
-        fetch_channels(head + nb, nb2);
         if constexpr (GEO) __syncthreads();
-        // Splats are taken in pairs: the twelve sums of a pair share one
-        // reduce-scatter and one atomic instruction.
+        float gsum[2] = {0.f, 0.f};  // this lane's sum of each eight splats
 #pragma unroll
-        for (int k2 = 0; k2 < 16; k2 += 2) {
-            float a[2 * VG];
+        for (int q = 0; q < 16; q += 8) {
+            f32x4_t* const row = reinterpret_cast<f32x4_t*>(&wl[lane * ROW + q]);
+            float al[8], dy[8], w[8];
+            bool ok[8], any = false;
 #pragma unroll
-            for (int v = 0; v < 2 * VG; ++v) a[v] = 0.f;
-            bool any = false;
-            int gp[2] = {-1, -1};
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                // branch-free: slots past the batch are read (in bounds) and
-                // every result is selected, so stale records change nothing
-                const int k = k2 + u;
-                const int at = (head + k) & (kRing - 1);
-                const float4 s0 = ring.rec[at][0];
-                const float4 s1 = ring.rec[at][1];
-                gp[u] = k < nb ? ring.gid[at] : -1;
-                const int j = ring.pos[at];
+            for (int u = 0; u < 8; ++u) {
+                const int at = (head + q + u) & (kRing - 1);
+                const float4 s0 = ring.rec[at][0], s1 = ring.rec[at][1];
                 const PairEval e = eval_pair(P.px, P.py, s0.x, s0.y, s0.z, s0.w, s1.x, s1.y);
-                const bool contrib = k < nb && j < nl && e.alpha >= kAlphaMin;
-                const float om = 1.f - e.alpha;  // >= 0.01
-                const float rom = __builtin_amdgcn_rcpf(om);
-                const float Tk = T * rom;
-                const float wv = e.alpha * Tk;
-                if (GEO) {
-                    const float sd = sdl[lane * 17 + k];
-                    const float dalpha = Tk * sd - S * rom;
-                    const bool live = contrib && s1.y * e.G < kAlphaMax;
-                    const float dq = dalpha * s1.y * e.G * -0.5f;
-                    a[VG * u + 0] = live ? dalpha * e.G : 0.f;
-                    a[VG * u + 1] = live ? dq * e.dx * e.dx : 0.f;
-                    a[VG * u + 2] = live ? 2.f * dq * e.dx * e.dy : 0.f;
-                    a[VG * u + 3] = live ? dq * e.dy * e.dy : 0.f;
-                    a[VG * u + 4] = live ? -2.f * dq * (s0.z * e.dx + s0.w * e.dy) : 0.f;
-                    a[VG * u + 5] = live ? -2.f * dq * (s0.w * e.dx + s1.x * e.dy) : 0.f;
-                    S = contrib ? S + wv * sd : S;
-                }
-                T = contrib ? Tk : T;
-                const float w = contrib ? wv : 0.f;
-                any = any || contrib;
-                wl[lane * 17 + k] = w;
+                ok[u] = __float_as_int(s1.w) < nl && e.alpha >= kAlphaMin;
+                al[u] = ok[u] ? e.alpha : 0.f;
+                dy[u] = e.dy;
+                any = any || ok[u];
             }
-            if (GEO && k2 < nb && __ballot(any) != 0ull) {
-                reduce_scatter<2 * VG>(a, lane);
-                const int gid = my_split ? gp[1] : gp[0];
-                if (my_own && gid >= 0) unsafeAtomicAdd(g_base + (size_t)gid * g_stride, a[0]);
+            if (__ballot(any) == 0ull) {
+                row[0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                row[1] = row[0];
+                continue;
+            }
+            float a[24];
+            f32x4_t sd[2];
+            if constexpr (GEO) {
+                sd[0] = row[0];
+                sd[1] = row[1];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float rom = __builtin_amdgcn_rcpf(1.f - al[u]);  // 1 - alpha >= 0.01
+                const float b = al[u] * rom;
+                w[u] = b * T;
+                if constexpr (GEO) {
+                    const float s = ok[u] ? sd[u >> 2][u & 3] : 0.f;  // a colour may be infinite
+                    const float h = al[u] < kAlphaMax ? b * (T * s - S) : 0.f;
+                    S += w[u] * s;
+                    a[3 * u] = h;
+                    a[3 * u + 1] = h * dy[u];
+                    a[3 * u + 2] = h * dy[u] * dy[u];
+                }
+                T *= rom;
+            }
+            row[0] = f32x4_t{w[0], w[1], w[2], w[3]};
+            row[1] = f32x4_t{w[4], w[5], w[6], w[7]};
+            if constexpr (GEO) {
+                rs_step<24, 32>(a, (lane & 32) == 0);
+                rs_step<12, 16>(a, (lane & 16) == 0);
+                rs_step<6, 8>(a, (lane & 8) == 0);
+                const int k = q + (lane >> 3), at = (head + k) & (kRing - 1);
+                const float4 s0 = ring.rec[at][0];
+                const float C = ring.rec[at][1].x, dx = P.px - s0.x, hx = a[0] * dx;
+                float v[6] = {a[0], s0.w * hx + C * a[1], a[2], s0.z * hx + s0.w * a[1], a[1] * dx, hx * dx};
+                rs_step<6, 4>(v, (lane & 4) == 0);
+                rs_step<3, 2>(v, (lane & 2) == 0);
+                rs_step<2, 1>(v, (lane & 1) == 0);
+                gsum[q >> 3] = v[0];
             }
         }
         __syncthreads();
@@ -257,25 +330,60 @@ __global__ void __launch_bounds__(64) render_bwd_mfma_kernel(
         for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 16; ++kk) {
-            const float a = wl[(4 * kk + (lane >> 4)) * 17 + (lane & 15)];
+            const float a = wl[(4 * kk + (lane >> 4)) * ROW + (lane & 15)];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16x16x4(a, bg[nt][kk], acc[nt]);
         }
-        // acc[nt][r]: Gaussian slot 4 (lane / 16) + r, channel 16 nt + lane % 16
+        // every load of this round is complete past this point
+        store_channels();
+        fill(head + nb);
+        if constexpr (GEO) {
+            // the rows of the batch, gathered in LDS (the weights' rows are free):
+            // 16 lanes then add a splat's whole row
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 16; q += 8)
+                if (my_own) wl[(q + (lane >> 3)) * ROW + my_word] = gsum[q >> 3];
+            const int c = (lane & 15) - CS % 16;  // colour or depth column of this lane
+            if (c >= 0 && c < 4)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    wl[(4 * (lane >> 4) + r) * ROW + (c < 3 ? GW_COLOR + c : (int)GW_DEPTH)] = acc[CS / 16][r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int slot = 4 * r + (lane >> 4);
+                const uint32_t gs = (uint32_t)ring.gid[(head + slot) & (kRing - 1)];
+                const float v = wl[slot * ROW + (lane & 15)];
+                if (slot < nb && (lane & 15) < GW_USED) unsafeAtomicAdd(at_row<OFF>(geo, gs, GW_STRIDE, lane & 15), v);
+            }
+        }
+        // acc[nt][r]: Gaussian slot 4 (lane / 16) + r, column 16 nt + lane % 16.
+        // Two whole tiles of features: rows of 16 lanes are swapped so that 32
+        // lanes hold 32 consecutive features of one slot.
+        constexpr int PAIRS = EXACT ? CS / 32 : 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int slot = 4 * (lane >> 4) + r;
-            const int gs = slot < nb ? ring.gid[(head + slot) & (kRing - 1)] : -1;
-            if (gs < 0) continue;
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                // channel c of this lane: colour, depth (workspace row) or feature
-                const int c = 16 * nt + (lane & 15);
-                const bool ok = c < CH && (EXACT || c < 4 + csem) && (GEO || c >= 4);
-                float* const base = c < 3 ? d_colors + c : c == 3 ? geo + GW_DEPTH : d_features + (c - 4);
-                const int stride = c < 3 ? 3 : c == 3 ? (int)GW_STRIDE : fstride;
-                const float v = acc[nt][r];
-                if (ok && v != 0.f) unsafeAtomicAdd(base + (size_t)gs * stride, v);
+            for (int pr = 0; pr < PAIRS; ++pr) {
+                const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[2 * pr][r]),
+                                                               __float_as_uint(acc[2 * pr + 1][r]), false, false);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int slot = 4 * (2 * (lane >> 5) + h) + r;
+                    const uint32_t gs = (uint32_t)ring.gid[(head + slot) & (kRing - 1)];
+                    if (slot < nb)
+                        unsafeAtomicAdd(at_row<OFF>(d_features, gs, fstride, 32 * pr + (lane & 31)),
+                                        __uint_as_float(x[h]));
+                }
+            }
+            const int slot = 4 * (lane >> 4) + r;
+            const uint32_t gs = (uint32_t)ring.gid[(head + slot) & (kRing - 1)];
+#pragma unroll
+            for (int nt = 2 * PAIRS; nt < (CS + 15) / 16; ++nt) {
+                const int j = 16 * nt + (lane & 15);
+                if (slot < nb && (16 * nt + 16 <= CS || j < CS) && (EXACT || j < csem))
+                    unsafeAtomicAdd(at_row<OFF>(d_features, gs, fstride, j), acc[nt][r]);
             }
         }
         __syncthreads();
@@ -304,8 +412,11 @@ __device__ __forceinline__ void cam_adjoint(int64_t i, const float* __restrict__
                                             const float* __restrict__ log_scales,
                                             const float4* __restrict__ quats, const float4* __restrict__ splat,
                                             const float* __restrict__ gw, const CamDevB& c, CamAdj& a) {
+    const float4 s0 = splat[2 * i], s1 = splat[2 * i + 1];
+    const float K00 = s0.z, K01 = s0.w, K11 = s1.x;
+    // dL/dconic: q = A dx^2 + 2 B dx dy + C dy^2 and dL/dq = -h / 2
     const float gmx = gw[GW_MX], gmy = gw[GW_MY];
-    const float gA = gw[GW_A], gB = gw[GW_B], gC = gw[GW_C], gd = gw[GW_DEPTH];
+    const float gA = -0.5f * gw[GW_XX], gB = -gw[GW_XY], gC = -0.5f * gw[GW_YY], gd = gw[GW_DEPTH];
     const float mx = means[3 * i], my = means[3 * i + 1], mz = means[3 * i + 2];
     const float px = c.R[0] * mx + c.R[1] * my + c.R[2] * mz + c.t[0];
     const float py = c.R[3] * mx + c.R[4] * my + c.R[5] * mz + c.t[1];
@@ -337,9 +448,7 @@ __device__ __forceinline__ void cam_adjoint(int64_t i, const float* __restrict__
     const float tx = fminf(fmaxf(u, -c.limx), c.limx) * pz;
     const float ty = fminf(fmaxf(v, -c.limy), c.limy) * pz;
     const float J[2][3] = {{c.fx * iz, 0.f, -c.fx * tx * iz * iz}, {0.f, c.fy * iz, -c.fy * ty * iz * iz}};
-    // conic = (A, B, C) from the splat record; dSigma' = -K Ghat K
-    const float4 s0 = splat[2 * i], s1 = splat[2 * i + 1];
-    const float K00 = s0.z, K01 = s0.w, K11 = s1.x;
+    // conic K = (A, B, C) from the splat record; dSigma' = -K Ghat K
     const float G00 = gA, G01 = 0.5f * gB, G11 = gC;
     const float KG00 = K00 * G00 + K01 * G01, KG01 = K00 * G01 + K01 * G11;
     const float KG10 = K01 * G00 + K11 * G01, KG11 = K01 * G01 + K11 * G11;
@@ -374,19 +483,23 @@ __device__ __forceinline__ void cam_adjoint(int64_t i, const float* __restrict__
 }
 
 // Per-Gaussian chain rule from (mean2d, conic, depth) to (mean, log-scale,
-// quaternion); the forward quantities are recomputed from the parameters.
+// quaternion), and the opacity's gradient; the forward quantities are
+// recomputed from the parameters.
 __global__ void __launch_bounds__(256) project_bwd_kernel(
     int64_t n, const float* __restrict__ means, const float* __restrict__ log_scales,
     const float4* __restrict__ quats, const int32_t* __restrict__ radius,
     const float4* __restrict__ splat, const float* __restrict__ geo, CamDevB c,
-    float* __restrict__ d_means, float* __restrict__ d_ls, float4* __restrict__ d_quats) {
+    float* __restrict__ d_means, float* __restrict__ d_ls, float4* __restrict__ d_quats,
+    float* __restrict__ d_opacity, float* __restrict__ d_colors) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    float gm[3] = {0.f, 0.f, 0.f}, gl[3] = {0.f, 0.f, 0.f};
+    float gm[3] = {0.f, 0.f, 0.f}, gl[3] = {0.f, 0.f, 0.f}, gc[3] = {0.f, 0.f, 0.f}, go = 0.f;
     float4 gq = make_float4(0.f, 0.f, 0.f, 0.f);
     if (radius[i] > 0) {
         CamAdj a;
         cam_adjoint(i, means, log_scales, quats, splat, geo + (size_t)i * GW_STRIDE, c, a);
+        go = geo[(size_t)i * GW_STRIDE + GW_1] / splat[2 * i + 1].y;  // da/do = a / o where not clamped
+        for (int k = 0; k < 3; ++k) gc[k] = geo[(size_t)i * GW_STRIDE + GW_COLOR + k];
         // dSigma = Rv^T dSc Rv
         float tmp[3][3], dSig[3][3];
         for (int r = 0; r < 3; ++r)
@@ -423,6 +536,8 @@ __global__ void __launch_bounds__(256) project_bwd_kernel(
     d_means[3 * i] = gm[0]; d_means[3 * i + 1] = gm[1]; d_means[3 * i + 2] = gm[2];
     d_ls[3 * i] = gl[0]; d_ls[3 * i + 1] = gl[1]; d_ls[3 * i + 2] = gl[2];
     d_quats[i] = gq;
+    d_opacity[i] = go;
+    d_colors[3 * i] = gc[0]; d_colors[3 * i + 1] = gc[1]; d_colors[3 * i + 2] = gc[2];
 }
 
 // Camera-pose gradient (Eq. (tracking): extrinsics optimised with the map
@@ -494,9 +609,16 @@ template <int CS, bool GEO, bool EXACT = true>
 static void launch_bwd(const xgs_gaussians* g, const xgs_projected* p, const xgs_binning* b,
                        const TileGrid& tg, const float* d_out, const float* final_T,
                        const int32_t* n_last, xgs_gaussians_grad* gr, float* geo, hipStream_t st) {
-    hipLaunchKernelGGL((render_bwd_mfma_kernel<CS, GEO, EXACT>), dim3(quad_blocks(tg)), dim3(64), 0, st, b->ranges,
-                       b->vals, reinterpret_cast<const float4*>(p->splat), g->colors, g->features, g->c_sem, tg,
-                       d_out, final_T, n_last, gr->colors, gr->features, gr->opacity, geo);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(quad_blocks(tg)), dim3(64), 0, st, b->ranges, b->vals,
+                           reinterpret_cast<const float4*>(p->splat), g->colors, g->features, g->c_sem, tg, d_out,
+                           final_T, n_last, gr->features, geo);
+    };
+    // the longest row of the arrays addressed is that of the features or of
+    // the workspace
+    const int64_t row = 4 * (int64_t)std::max<int>(g->c_sem, GW_STRIDE);
+    if (g->n * row <= (int64_t)UINT32_MAX) launch(render_bwd_mfma_kernel<CS, GEO, EXACT, uint32_t>);
+    else launch(render_bwd_mfma_kernel<CS, GEO, EXACT, uint64_t>);
 }
 
 template <bool GEO>
@@ -508,13 +630,17 @@ static void dispatch_bwd(const xgs_gaussians* g, const xgs_projected* p, const x
     switch (cs) {
 #define XGS_BWD_CASE(n) case n: launch_bwd<n, GEO>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st); return;
         XGS_BWD_CASE(1) XGS_BWD_CASE(2) XGS_BWD_CASE(3) XGS_BWD_CASE(4) XGS_BWD_CASE(8)
-        XGS_BWD_CASE(12) XGS_BWD_CASE(16) XGS_BWD_CASE(24) XGS_BWD_CASE(32) XGS_BWD_CASE(48)
+        XGS_BWD_CASE(12) XGS_BWD_CASE(16) XGS_BWD_CASE(20) XGS_BWD_CASE(24) XGS_BWD_CASE(28) XGS_BWD_CASE(32)
+        XGS_BWD_CASE(48)
 #undef XGS_BWD_CASE
         default: break;
     }
     if constexpr (GEO) {
         if (cs == 0) launch_bwd<0, true>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
+        else if (cs <= 12) launch_bwd<12, true, false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
         else if (cs <= 16) launch_bwd<16, true, false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
+        else if (cs <= 24) launch_bwd<24, true, false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
+        else if (cs <= 28) launch_bwd<28, true, false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
         else if (cs <= 32) launch_bwd<32, true, false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
         else launch_bwd<54, true, false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
     } else {
@@ -550,15 +676,13 @@ extern "C" size_t xgs_render_bwd_workspace(int64_t n) {
     return c.total();
 }
 
-// The accumulated gradients (features; with the geometry also colours,
-// opacity) and the geometry workspace rows start at zero: one launch.
+// The accumulated gradients (features; with the geometry the workspace rows,
+// from which the projection pass writes the others) start at zero: one launch.
 static xgs_status zero_accumulated(const xgs_gaussians* g, bool geo_on, xgs_gaussians_grad* gr, float* geo,
                                    hipStream_t st) {
     ZeroRanges zr{};
     if (g->c_sem > 0) { zr.p[zr.k] = reinterpret_cast<uint32_t*>(gr->features); zr.n[zr.k++] = g->n * g->c_sem; }
     if (geo_on) {
-        zr.p[zr.k] = reinterpret_cast<uint32_t*>(gr->colors); zr.n[zr.k++] = 3 * g->n;
-        zr.p[zr.k] = reinterpret_cast<uint32_t*>(gr->opacity); zr.n[zr.k++] = g->n;
         zr.p[zr.k] = reinterpret_cast<uint32_t*>(geo); zr.n[zr.k++] = GW_STRIDE * g->n;
     }
     return zero_ranges(zr, st);
@@ -633,7 +757,7 @@ extern "C" xgs_status xgs_render_bwd(const xgs_gaussians* g, const xgs_projected
         hipLaunchKernelGGL(project_bwd_kernel, dim3((unsigned)((g->n + 255) / 256)), dim3(256), 0, st, g->n,
                            g->means, g->log_scales, reinterpret_cast<const float4*>(g->quats), p->radius,
                            reinterpret_cast<const float4*>(p->splat), geo, c, gr->means, gr->log_scales,
-                           reinterpret_cast<float4*>(gr->quats));
+                           reinterpret_cast<float4*>(gr->quats), gr->opacity, gr->colors);
         return check_launch("xgs_render_bwd projection");
     }
     dispatch_bwd<false>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);

@@ -123,9 +123,8 @@ __device__ __forceinline__ bool quad_hit(const float4 s0, const float4 s1, const
 constexpr int kRing = 128;
 
 struct Ring {
-    float4 rec[kRing][2];
+    float4 rec[kRing][2];  // the splat record, its last word the list position (bits of an int)
     int gid[kRing];
-    int pos[kRing];  // list position (offset from the tile's start)
 };
 
 // Appends this lane's candidate when keep is set; returns the new tail.
@@ -135,9 +134,8 @@ __device__ __forceinline__ int ring_push(Ring& q, int tail, bool keep, float4 s0
         const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
         const int at = (tail + below) & (kRing - 1);
         q.rec[at][0] = s0;
-        q.rec[at][1] = s1;
+        q.rec[at][1] = make_float4(s1.x, s1.y, s1.z, __int_as_float(pos));
         q.gid[at] = gid;
-        q.pos[at] = pos;
     }
     return tail + __popcll(m);
 }

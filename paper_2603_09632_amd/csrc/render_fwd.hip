@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS > 32
             nz |= contrib ? (1u << k) : 0u;
             wl[lane * 17 + k] = w;
         }
-        if (lastk >= 0) last = ring.pos[(head + lastk) & (kRing - 1)] + 1;
+        if (lastk >= 0) last = __float_as_int(ring.rec[(head + lastk) & (kRing - 1)][1].w) + 1;
         head += nb;
         __syncthreads();
         // a 16-pixel x 4-splat block of weights that is all zero adds nothing
