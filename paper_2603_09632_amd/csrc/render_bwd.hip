@@ -14,7 +14,6 @@
 // conic = Sigma'^-1, Sigma' = J Sigma_cam J^T + 0.3 I, Sigma_cam = Rv Sigma Rv^T,
 // Sigma = (R S)(R S)^T, p = Rv mu + t (App. A).
 #include <algorithm>
-#include <type_traits>
 
 #include "render_common.h"
 #include "sort.h"
@@ -67,14 +66,6 @@ enum { GW_MX = 0, GW_MY = 1, GW_XX = 2, GW_XY = 3, GW_YY = 4, GW_1 = 5, GW_DEPTH
 // product W^T G on v_mfma_f32_16x16x4_f32 (features first, then
 // colour and depth), and
 // the batch's g.c another; g.c and then w go through one LDS array.
-// OFF: the type of a byte offset into the per-Gaussian rows: 32 bits where they
-// all fit (an address is then one scalar base and one register).
-template <typename OFF, typename T>
-__device__ __forceinline__ T* at_row(T* base, uint32_t row, int stride, int word) {
-    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte;
-    return reinterpret_cast<T*>(reinterpret_cast<byte*>(base) + ((OFF)row * (OFF)(4 * stride) + (OFF)(4 * word)));
-}
-
 template <int CS, bool GEO, bool EXACT, typename OFF>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 16 ? 3 : 1))) render_bwd_mfma_kernel(
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
@@ -169,15 +160,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
             cn = entry(cpos - 64);
         }
         if (cpos <= 0 && !padded) {
-            // sixteen slots that no pixel takes follow the last splat, so that
-            // the walk need not look at a batch's size
             padded = true;
-            if (lane < 16) {
-                const int at = (tail + lane) & (kRing - 1);
-                ring.rec[at][0] = make_float4(0.f, 0.f, 0.f, 0.f);
-                ring.rec[at][1] = make_float4(0.f, 0.f, 0.f, __int_as_float(0x7FFFFFFF));
-                ring.gid[at] = cg;
-            }
+            ring_pad(ring, tail, lane, cg);
         }
     };
     // Channel rows of a batch (only the S = C G^T product reads them): lane
@@ -186,7 +170,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
     // 4-byte alignment: a row may start anywhere.)  Other rows are read as 64
     // consecutive (splat, feature) pairs per load.  Slots past the batch hold
     // the index of some splat; nothing of them is used.
-    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     constexpr bool QUADS = EXACT && CS % 4 == 0;
     constexpr int GRP = QUADS ? (CS + 15) / 16 : 0;
     constexpr int PERF = QUADS ? 0 : (16 * CS + 63) / 64;

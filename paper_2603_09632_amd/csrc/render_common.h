@@ -1,5 +1,7 @@
 // Shared launch geometry of the forward and backward compositing kernels.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace xgs {
@@ -138,6 +140,36 @@ __device__ __forceinline__ int ring_push(Ring& q, int tail, bool keep, float4 s0
         q.gid[at] = gid;
     }
     return tail + __popcll(m);
+}
+
+// Sixteen slots that no pixel takes (alpha 0, list position past any other; the
+// index gid is in bounds) after the last splat of a list, so that a walk need
+// not look at a batch's size.
+__device__ __forceinline__ void ring_pad(Ring& q, int tail, int lane, int gid) {
+    if (lane < 16) {
+        const int at = (tail + lane) & (kRing - 1);
+        q.rec[at][0] = make_float4(0.f, 0.f, 0.f, 0.f);
+        q.rec[at][1] = make_float4(0.f, 0.f, 0.f, __int_as_float(0x7FFFFFFF));
+        q.gid[at] = gid;
+    }
+}
+
+// Word `word` of row `row` of an array of rows of `stride` words.  OFF: the type
+// of the byte offset, 32 bits where every row's fits (an address is then one
+// scalar base and one register).
+template <typename OFF, typename T>
+__device__ __forceinline__ T* at_row(T* base, uint32_t row, int stride, int word) {
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte;
+    return reinterpret_cast<T*>(reinterpret_cast<byte*>(base) + ((OFF)row * (OFF)(4 * stride) + (OFF)(4 * word)));
+}
+
+// Four floats at any 4-byte alignment.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// 4x4x1 FP32 matrix core op, sixteen blocks: lane l supplies A[l % 4] and B[l % 4]
+// of block l / 4, and the accumulator holds D[r][l % 4] of that block, r = 0..3.
+__device__ __forceinline__ f32x4_t mfma4x4x1(float a, float b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
 }
 
 // 16x16x4 FP32 matrix core op: lane l supplies A[l % 16][l / 16] and
