@@ -225,8 +225,12 @@ xgs_status xgs_render_fwd(const xgs_gaussians* g, const xgs_projected* p, const 
  * projection.  grads: all six arrays are overwritten (the call zeroes them).
  * flags: XGS_BWD_FEATURES_ONLY computes only d_features (geometry frozen,
  * Sec. 3.2.2 "decouple"); the other gradient pointers may then be NULL.
- * ws must hold xgs_render_bwd_workspace(n) bytes, 256-byte aligned. */
-enum { XGS_BWD_ALL = 0, XGS_BWD_FEATURES_ONLY = 1, XGS_BWD_PREZEROED = 2 };
+ * ws must hold xgs_render_bwd_workspace(n) bytes, 256-byte aligned.
+ * XGS_BWD_POSE computes only the workspace rows that xgs_pose_grad reads, from
+ * the colour and depth channels of d_out (the semantic ones count as zero and
+ * are not read; d_out may end after channel 3); all gradient pointers may be
+ * NULL.  Not with XGS_BWD_PREZEROED. */
+enum { XGS_BWD_ALL = 0, XGS_BWD_FEATURES_ONLY = 1, XGS_BWD_PREZEROED = 2, XGS_BWD_POSE = 4 };
 size_t xgs_render_bwd_workspace(int64_t n);
 /* The zeroing that xgs_render_bwd does first, as a call of its own: the
  * accumulated gradients (features) and, with XGS_BWD_ALL, the workspace's
@@ -330,7 +334,7 @@ xgs_status xgs_grid_sample_offsets(const float* P, int32_t D, int32_t Hf, int32_
  *   d_pose[3..5] = sum_i [ p_i x dL/dp_i + axial(Sc_i G_i - G_i Sc_i) ],
  * p_i camera-space mean, Sc_i camera covariance, G_i = dL/dSc_i,
  * axial(A) = (A_23 - A_32, A_31 - A_13, A_12 - A_21).
- * Call after xgs_render_bwd (XGS_BWD_ALL) on the same stream with the same
+ * Call after xgs_render_bwd (XGS_BWD_ALL or XGS_BWD_POSE) on the same stream with the same
  * g, p, cam and ws: it reads the per-Gaussian image-space adjoints that pass
  * leaves in ws.  d_pose: 6 device floats.  Deterministic (fixed order). */
 xgs_status xgs_pose_grad(const xgs_gaussians* g, const xgs_projected* p, const xgs_camera* cam,

@@ -28,7 +28,7 @@ SPLAT_STRIDE = 8
 GRID_BILINEAR, GRID_NEAREST = 0, 1
 VQ_FP32, VQ_BF16_RESCORE4 = 0, 1
 EMA_PAPER, EMA_LAPLACE = 0, 1
-BWD_ALL, BWD_FEATURES_ONLY, BWD_PREZEROED = 0, 1, 2
+BWD_ALL, BWD_FEATURES_ONLY, BWD_PREZEROED, BWD_POSE = 0, 1, 2, 4
 
 __all__ = [
     "XgsError", "Gaussians", "Projected", "Binning", "camera", "camera_from", "grid_dims",
@@ -328,12 +328,16 @@ def xgs_render_fwd(g: Gaussians, p: Projected, b: Binning, cam, out=None, final_
 def xgs_render_bwd(g: Gaussians, p: Projected, b: Binning, cam, d_out, final_T, n_last,
                    flags: int = BWD_ALL, grads: Optional[Gaussians] = None, workspace=None,
                    stream=None) -> Gaussians:
+    """BWD_POSE (rows for xgs_pose_grad only, into ``workspace``) has no gradients
+    to return."""
     c = camera_from(cam)
-    grads = grads or Gaussians.empty_like(g)
+    if flags != BWD_POSE:
+        grads = grads or Gaussians.empty_like(g)
     need = int(lib.xgs_render_bwd_workspace(g.n))
     if workspace is None or workspace.numel() < need:
         workspace = torch.empty(need, dtype=torch.uint8, device=g.means.device)
-    gs, ps, bs, gr = g.struct(), p.struct(), b.struct(), grads.struct()
+    gs, ps, bs = g.struct(), p.struct(), b.struct()
+    gr = grads.struct() if flags != BWD_POSE else XgsGaussians(n=g.n, c_sem=g.c_sem)
     check(lib.xgs_render_bwd(ctypes.byref(gs), ctypes.byref(ps), ctypes.byref(bs), ctypes.byref(c), _ptr(d_out),
                              _ptr(final_T), _ptr(n_last), int(flags), ctypes.byref(gr), _ptr(workspace),
                              workspace.numel(), _stream(stream)), "xgs_render_bwd")
@@ -474,11 +478,11 @@ def tracking_step(g: Gaussians, p: Projected, b: Binning, cam, image: torch.Tens
     ``b`` must come from xgs_project / xgs_tile_sort at ``cam``.  Returns
     (loss [1], dL/dxi [6], rendered map)."""
     out, fT, nl = xgs_render_fwd(g, p, b, cam, stream=stream)
-    loss, d_out = xgs_tracking_loss(out, image, depth, lam_d, stream=stream)
+    loss, d_out = xgs_tracking_loss(out[:4], image, depth, lam_d, stream=stream)
     need = int(lib.xgs_render_bwd_workspace(g.n))
     if workspace is None or workspace.numel() < need:
         workspace = torch.empty(need, dtype=torch.uint8, device=g.means.device)
-    xgs_render_bwd(g, p, b, cam, d_out, fT, nl, workspace=workspace, stream=stream)
+    xgs_render_bwd(g, p, b, cam, d_out, fT, nl, flags=BWD_POSE, workspace=workspace, stream=stream)
     d_pose = xgs_pose_grad(g, p, cam, workspace, stream=stream)
     return loss, d_pose, out
 

@@ -66,7 +66,15 @@ enum { GW_MX = 0, GW_MY = 1, GW_XX = 2, GW_XY = 3, GW_YY = 4, GW_1 = 5, GW_DEPTH
 // product W^T G on v_mfma_f32_16x16x4_f32 (features first, then
 // colour and depth), and
 // the batch's g.c another; g.c and then w go through one LDS array.
-template <int CS, bool GEO, bool EXACT, typename OFF>
+//
+// POSE (CS = 0): only the sums that the pose gradient reads.  The semantic
+// channels' upstream gradient is taken as zero (they are not read), no channel
+// gradient but the depth's is formed, and that one as a fourth sum per splat
+// (w g_depth) instead of a product; a splat's seven sums are added from eight
+// lanes.  The kernel on 1M Gaussians, 1200 x 680, 32 features:
+// 347 us with every gradient, 135 so; with the zeroing and the projection pass
+// that a pose needs no more, a tracking step 657 -> 351 us.
+template <int CS, bool GEO, bool EXACT, typename OFF, bool POSE = false>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 16 ? 3 : 1))) render_bwd_mfma_kernel(
     const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float4* __restrict__ splat, const float* __restrict__ colors,
@@ -75,7 +83,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
     float* __restrict__ d_features, float* __restrict__ geo) {
     constexpr int CH = 4 + CS;
     constexpr int CHP = (CH + 3) / 4 * 4;           // LDS row stride (float4 rows)
-    constexpr int COLS = GEO ? CH : CS;             // columns of W^T G: features, then colour and depth
+    constexpr int COLS = POSE ? 0 : GEO ? CH : CS;  // columns of W^T G: features, then colour and depth
     constexpr int NT = (COLS + 15) / 16;
     constexpr int ROW = 20;                         // LDS row of a pixel: 16 splats, float4-aligned, banks spread
     __shared__ __align__(16) float wl[64 * ROW];    // g.c of (pixel, splat), then its weight
@@ -87,14 +95,16 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
     const int lane = threadIdx.x;
     // the sum that ends on this lane after the column reduce-scatter (ids: 0 h,
     // 1 mean y, 2 h dy^2, 3 mean x, 4 h dx dy, 5 h dx^2), as its place in the row
-    const int id = 3 * ((lane >> 2) & 1) + ((lane & 1) ? 2 : (lane >> 1) & 1);
-    const bool my_own = (lane & 3) != 3;
-    const int my_word = id == 0 ? GW_1 : id == 1 ? GW_MY : id == 2 ? GW_YY : id == 3 ? GW_MX : id == 4 ? GW_XY : GW_XX;
+    // (POSE: also 6 depth)
+    const int id = POSE ? ((lane & 7) == 3 ? 6 : 3 * ((lane >> 2) & 1) + (lane & 3))
+                        : 3 * ((lane >> 2) & 1) + ((lane & 1) ? 2 : (lane >> 1) & 1);
+    const bool my_own = POSE ? (lane & 7) != 7 : (lane & 3) != 3;
+    const int my_word = id == 6 ? GW_DEPTH : id == 0 ? GW_1 : id == 1 ? GW_MY : id == 2 ? GW_YY : id == 3 ? GW_MX : id == 4 ? GW_XY : GW_XX;
     const size_t hw = (size_t)g.hs * g.ws;
     const int fstride = EXACT ? CS : csem;
     const int qx = P.n - (lane & 7), qy = P.m - (lane >> 3);  // quadrant origin
     // upstream gradients in B-operand layout: pixel 4 kk + lane / 16, channel 16 nt + lane % 16
-    float bg[NT][16];
+    float bg[NT > 0 ? NT : 1][16];
 #pragma unroll
     for (int kk = 0; kk < 16; ++kk) {
         const int p = 4 * kk + (lane >> 4);
@@ -123,12 +133,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
                 gt[kc][nt] = use ? d_out[c * hw + (size_t)m * g.ws + n] : 0.f;
             }
     }
-    float T = 1.f;
+    float T = 1.f, gdepth = 0.f;
     int nl = 0;
     if (P.inside) {
         const size_t pix = (size_t)P.m * g.ws + P.n;
         T = final_T[pix];
         nl = n_last[pix];
+        if (POSE) gdepth = d_out[3 * hw + pix];
     }
     int jmax = nl;
 #pragma unroll
@@ -270,7 +281,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
                 row[1] = row[0];
                 continue;
             }
-            float a[24];
+            constexpr int V = POSE ? 4 : 3;  // sums of a splat over the rows
+            float a[8 * V];
             f32x4_t sd[2];
             if constexpr (GEO) {
                 sd[0] = row[0];
@@ -285,34 +297,39 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
                     const float s = ok[u] ? sd[u >> 2][u & 3] : 0.f;  // a colour may be infinite
                     const float h = al[u] < kAlphaMax ? b * (T * s - S) : 0.f;
                     S += w[u] * s;
-                    a[3 * u] = h;
-                    a[3 * u + 1] = h * dy[u];
-                    a[3 * u + 2] = h * dy[u] * dy[u];
+                    a[V * u] = h;
+                    a[V * u + 1] = h * dy[u];
+                    a[V * u + 2] = h * dy[u] * dy[u];
+                    if constexpr (POSE) a[V * u + 3] = w[u] * (ok[u] ? gdepth : 0.f);
                 }
                 T *= rom;
             }
-            row[0] = f32x4_t{w[0], w[1], w[2], w[3]};
-            row[1] = f32x4_t{w[4], w[5], w[6], w[7]};
+            if constexpr (!POSE) {
+                row[0] = f32x4_t{w[0], w[1], w[2], w[3]};
+                row[1] = f32x4_t{w[4], w[5], w[6], w[7]};
+            }
             if constexpr (GEO) {
-                rs_step<24, 32>(a, (lane & 32) == 0);
-                rs_step<12, 16>(a, (lane & 16) == 0);
-                rs_step<6, 8>(a, (lane & 8) == 0);
+                rs_step<8 * V, 32>(a, (lane & 32) == 0);
+                rs_step<4 * V, 16>(a, (lane & 16) == 0);
+                rs_step<2 * V, 8>(a, (lane & 8) == 0);
                 const int k = q + (lane >> 3), at = (head + k) & (kRing - 1);
                 const float4 s0 = ring.rec[at][0];
                 const float C = ring.rec[at][1].x, dx = P.px - s0.x, hx = a[0] * dx;
-                float v[6] = {a[0], s0.w * hx + C * a[1], a[2], s0.z * hx + s0.w * a[1], a[1] * dx, hx * dx};
-                rs_step<6, 4>(v, (lane & 4) == 0);
-                rs_step<3, 2>(v, (lane & 2) == 0);
+                float v[3 + V] = {a[0], s0.w * hx + C * a[1], a[2], s0.z * hx + s0.w * a[1], a[1] * dx, hx * dx};
+                if constexpr (POSE) v[6] = a[3];
+                rs_step<3 + V, 4>(v, (lane & 4) == 0);
+                rs_step<V, 2>(v, (lane & 2) == 0);
                 rs_step<2, 1>(v, (lane & 1) == 0);
                 gsum[q >> 3] = v[0];
             }
         }
         __syncthreads();
-        f32x4_t acc[NT];
+        f32x4_t acc[NT > 0 ? NT : 1];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 16; ++kk) {
+            if constexpr (NT == 0) break;
             const float a = wl[(4 * kk + (lane >> 4)) * ROW + (lane & 15)];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma16x16x4(a, bg[nt][kk], acc[nt]);
@@ -320,7 +337,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
         // every load of this round is complete past this point
         store_channels();
         fill(head + nb);
-        if constexpr (GEO) {
+        if constexpr (POSE) {
+#pragma unroll
+            for (int q = 0; q < 16; q += 8) {
+                const int k = q + (lane >> 3);
+                const uint32_t gs = (uint32_t)ring.gid[(head + k) & (kRing - 1)];
+                if (my_own && k < nb) unsafeAtomicAdd(at_row<OFF>(geo, gs, GW_STRIDE, my_word), gsum[q >> 3]);
+            }
+        } else if constexpr (GEO) {
             // the rows of the batch, gathered in LDS (the weights' rows are free):
             // 16 lanes then add a splat's whole row
             __syncthreads();
@@ -529,7 +553,7 @@ __global__ void __launch_bounds__(256) project_bwd_kernel(
 // Sigma_cam phi^, so per Gaussian dL/drho = dL/dp and
 // dL/dphi = p x dL/dp + axial(Sc G - G Sc), G = dL/dSigma_cam,
 // axial(A) = (A_23 - A_32, A_31 - A_13, A_12 - A_21).  Each workgroup sums
-// its 256 Gaussians in a fixed tree order into partial[block][6].
+// 256 Gaussians in a fixed tree order into partial[block][6].
 __global__ void __launch_bounds__(256) pose_grad_kernel(
     int64_t n, const float* __restrict__ means, const float* __restrict__ log_scales,
     const float4* __restrict__ quats, const int32_t* __restrict__ radius, const float4* __restrict__ splat,
@@ -588,7 +612,7 @@ __global__ void __launch_bounds__(256) pose_total_kernel(const float* __restrict
     if (t < 6) d_pose[t] = red[t][0];
 }
 
-template <int CS, bool GEO, bool EXACT = true>
+template <int CS, bool GEO, bool EXACT = true, bool POSE = false>
 static void launch_bwd(const xgs_gaussians* g, const xgs_projected* p, const xgs_binning* b,
                        const TileGrid& tg, const float* d_out, const float* final_T,
                        const int32_t* n_last, xgs_gaussians_grad* gr, float* geo, hipStream_t st) {
@@ -600,8 +624,8 @@ static void launch_bwd(const xgs_gaussians* g, const xgs_projected* p, const xgs
     // the longest row of the arrays addressed is that of the features or of
     // the workspace
     const int64_t row = 4 * (int64_t)std::max<int>(g->c_sem, GW_STRIDE);
-    if (g->n * row <= (int64_t)UINT32_MAX) launch(render_bwd_mfma_kernel<CS, GEO, EXACT, uint32_t>);
-    else launch(render_bwd_mfma_kernel<CS, GEO, EXACT, uint64_t>);
+    if (g->n * row <= (int64_t)UINT32_MAX) launch(render_bwd_mfma_kernel<CS, GEO, EXACT, uint32_t, POSE>);
+    else launch(render_bwd_mfma_kernel<CS, GEO, EXACT, uint64_t, POSE>);
 }
 
 template <bool GEO>
@@ -661,11 +685,17 @@ extern "C" size_t xgs_render_bwd_workspace(int64_t n) {
 
 // The accumulated gradients (features; with the geometry the workspace rows,
 // from which the projection pass writes the others) start at zero: one launch.
-static xgs_status zero_accumulated(const xgs_gaussians* g, bool geo_on, xgs_gaussians_grad* gr, float* geo,
-                                   hipStream_t st) {
+// radius (may be NULL): only the workspace rows of the Gaussians in view, the
+// only ones that are read again (of 1M Gaussians of a room about one in eight:
+// 9 MB instead of 64).
+static xgs_status zero_accumulated(const xgs_gaussians* g, bool features, bool geo_on, xgs_gaussians_grad* gr,
+                                   float* geo, const int32_t* radius, hipStream_t st) {
     ZeroRanges zr{};
-    if (g->c_sem > 0) { zr.p[zr.k] = reinterpret_cast<uint32_t*>(gr->features); zr.n[zr.k++] = g->n * g->c_sem; }
+    if (features && g->c_sem > 0) { zr.p[zr.k] = reinterpret_cast<uint32_t*>(gr->features); zr.n[zr.k++] = g->n * g->c_sem; }
     if (geo_on) {
+        static_assert(GW_STRIDE == ZeroRanges::kRow, "workspace rows");
+        zr.seen = radius;
+        zr.seen_k = zr.k;
         zr.p[zr.k] = reinterpret_cast<uint32_t*>(geo); zr.n[zr.k++] = GW_STRIDE * g->n;
     }
     return zero_ranges(zr, st);
@@ -686,7 +716,7 @@ extern "C" xgs_status xgs_render_bwd_zero(const xgs_gaussians* g, int32_t flags,
     if (g->n == 0) return XGS_OK;
     if ((g->c_sem > 0 && !gr->features) || (geo_on && (!gr->colors || !gr->opacity)))
         return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd_zero: null gradient array");
-    xgs_status s = zero_accumulated(g, geo_on, gr, static_cast<float*>(ws), (hipStream_t)stream);
+    xgs_status s = zero_accumulated(g, true, geo_on, gr, static_cast<float*>(ws), nullptr, (hipStream_t)stream);
     if (s) return s;
     return check_launch("xgs_render_bwd_zero");
 }
@@ -701,9 +731,9 @@ extern "C" xgs_status xgs_render_bwd(const xgs_gaussians* g, const xgs_projected
     if (xgs_status s = validate_camera(cam)) return s;
     const bool prezeroed = (flags & XGS_BWD_PREZEROED) != 0;
     flags &= ~XGS_BWD_PREZEROED;
-    if (flags != XGS_BWD_ALL && flags != XGS_BWD_FEATURES_ONLY)
+    if (flags != XGS_BWD_ALL && flags != XGS_BWD_FEATURES_ONLY && (flags != XGS_BWD_POSE || prezeroed))
         return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd: unknown flags");
-    const bool geo_on = flags == XGS_BWD_ALL;
+    const bool pose = flags == XGS_BWD_POSE, geo_on = flags != XGS_BWD_FEATURES_ONLY;
     if (g->c_sem < 0 || g->c_sem > XGS_MAX_C_SEM)
         return fail(XGS_ERR_UNSUPPORTED, "xgs_render_bwd: c_sem must be in [0, 64]");
     if (geo_on && g->c_sem > 54)
@@ -714,12 +744,12 @@ extern "C" xgs_status xgs_render_bwd(const xgs_gaussians* g, const xgs_projected
     if (g->n > 0) {
         if (!g->colors || (g->c_sem > 0 && !g->features) || !p->splat || !p->radius)
             return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd: null Gaussian array");
-        if (g->c_sem > 0 && !gr->features)
+        if (!pose && g->c_sem > 0 && !gr->features)
             return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd: null feature gradient");
-        if (geo_on && (!gr->means || !gr->log_scales || !gr->quats || !gr->opacity || !gr->colors ||
+        if (geo_on && !pose && (!gr->means || !gr->log_scales || !gr->quats || !gr->opacity || !gr->colors ||
                        !g->means || !g->log_scales || !g->quats))
             return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd: null gradient array");
-        if (geo_on && !aligned(gr->quats, 16))
+        if (geo_on && !pose && !aligned(gr->quats, 16))
             return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd: quats gradient must be 16-byte aligned");
     }
     if (!aligned(ws, 256)) return fail(XGS_ERR_INVALID_ARG, "xgs_render_bwd: workspace must be 256-byte aligned");
@@ -729,10 +759,14 @@ extern "C" xgs_status xgs_render_bwd(const xgs_gaussians* g, const xgs_projected
     hipStream_t st = (hipStream_t)stream;
     float* geo = static_cast<float*>(ws);
     xgs_status s;
-    // the accumulated gradients and the geometry workspace start at zero (one
-    // launch), unless the caller had xgs_render_bwd_zero do it beforehand
-    if (!prezeroed && (s = zero_accumulated(g, geo_on, gr, geo, st))) return s;
+    // the accumulated gradients and the workspace rows start at zero, unless the
+    // caller had xgs_render_bwd_zero do it beforehand
+    if (!prezeroed && (s = zero_accumulated(g, !pose, geo_on, gr, geo, p->radius, st))) return s;
     TileGrid tg = tile_grid(*cam, b->tile_order);
+    if (pose) {
+        launch_bwd<0, true, true, true>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
+        return check_launch("xgs_render_bwd pose");
+    }
     if (geo_on) {
         dispatch_bwd<true>(g, p, b, tg, d_out, final_T, n_last, gr, geo, st);
         if ((s = check_launch("xgs_render_bwd pixels"))) return s;

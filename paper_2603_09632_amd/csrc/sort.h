@@ -73,6 +73,11 @@ struct ZeroRanges {
     uint32_t* p[4];
     int64_t n[4];
     int k;
+    // optional: of range seen_k, rows of kRow words at 16-byte alignment, only
+    // those whose seen[row] is above 0
+    static constexpr int kRow = 16;
+    const int32_t* seen;
+    int seen_k;
 };
 xgs_status zero_ranges(const ZeroRanges& r, hipStream_t stream);
 

@@ -27,6 +27,12 @@ __global__ void zero_ranges_kernel(ZeroRanges r) {
     const int64_t n = r.n[blockIdx.y];
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    if (r.seen && (int)blockIdx.y == r.seen_k) {  // uniform
+        uint4* rows = reinterpret_cast<uint4*>(p);
+        for (int64_t i = t0; i < n / 4; i += stride)
+            if (r.seen[i / (ZeroRanges::kRow / 4)] > 0) rows[i] = make_uint4(0u, 0u, 0u, 0u);
+        return;
+    }
     const int64_t head = (int64_t)(((16 - ((uintptr_t)p & 15)) & 15) / 4);  // words before 16-byte alignment
     const int64_t h = head < n ? head : n;
     const int64_t nv = (n - h) / 4;
