@@ -79,17 +79,53 @@ __global__ void __launch_bounds__(256) sem_softmax_bwd_kernel(const float* __res
 }
 
 // ------------------------------------------------------------- valid count
-__global__ void __launch_bounds__(256) sem_count_kernel(const uint8_t* __restrict__ V, int64_t P,
-                                                       int* __restrict__ count) {
+// Valid pixels, one sum per block (kCountBlocks of them; the loss kernels add
+// them up, one per lane).  One atomic per wavefront on one counter took 43 us at
+// 640 x 480, this 4.7.
+constexpr int kCountBlocks = 64;
+
+__global__ void __launch_bounds__(1024) sem_count_kernel(const uint8_t* __restrict__ V, int64_t P,
+                                                        int* __restrict__ counts) {
+    __shared__ int red[16];
+    const int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x, stride = (int64_t)gridDim.x * 1024;
+    // bytes before 16-byte alignment, 16-byte words, the bytes after them
+    const int64_t head = min(P, (int64_t)((16 - ((uintptr_t)V & 15)) & 15)), body = (P - head) / 16;
     int c = 0;
-    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < P; p += (int64_t)gridDim.x * 256)
-        c += V[p] != 0;
+    auto nonzero = [](uint32_t w) {
+        return (int)((w & 0xFFu) != 0) + (int)((w & 0xFF00u) != 0) + (int)((w & 0xFF0000u) != 0) + (int)(w > 0xFFFFFFu);
+    };
+    for (int64_t q = t; q < body; q += stride) {
+        const uint4 v = reinterpret_cast<const uint4*>(V + head)[q];
+        c += nonzero(v.x) + nonzero(v.y) + nonzero(v.z) + nonzero(v.w);
+    }
+    if (t < head) c += V[t] != 0;
+    const int64_t tail0 = head + 16 * body;
+    if (t < P - tail0) c += V[tail0 + t] != 0;
     for (int k = 32; k >= 1; k >>= 1) c += __shfl_xor(c, k, 64);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(count, c);  // integer sum: order-independent
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int s = 0;
+        for (int k = 0; k < 16; ++k) s += red[k];
+        counts[blockIdx.x] = s;
+    }
 }
 
-__global__ void sem_zero_kernel(int* __restrict__ count) { *count = 0; }
-__global__ void sem_fill_count_kernel(int* __restrict__ count, int v) { *count = v; }
+// The number of valid pixels, in every lane: the sum of the blocks' counts, or
+// all P (at most INT_MAX) without a mask.
+__device__ __forceinline__ int valid_total(const uint8_t* V, const int* __restrict__ counts, int64_t P) {
+    if (!V) return (int)min(P, (int64_t)0x7FFFFFFF);
+    int n = counts[threadIdx.x & 63];
+    static_assert(kCountBlocks == 64, "one count per lane");
+    const int lane = threadIdx.x & 63;
+    n += xlane_partner<32>(n, lane);
+    n += xlane_partner<16>(n, lane);
+    n += xlane_partner<8>(n, lane);
+    n += xlane_partner<4>(n, lane);
+    n += xlane_partner<2>(n, lane);
+    n += xlane_partner<1>(n, lane);
+    return n;
+}
 
 // ----------------------------------------------------------- decode + loss
 // One workgroup: 64 SEM_NPT consecutive grid pixels, wavefront q taking
@@ -120,7 +156,7 @@ __global__ void __launch_bounds__(256) sem_loss_kernel(const float* __restrict__
                                                       const float* __restrict__ E,
                                                       const float* __restrict__ Gs,
                                                       const uint8_t* __restrict__ V, float lambda,
-                                                      const int* __restrict__ count,
+                                                      const int* __restrict__ counts,
                                                       float* __restrict__ d_out, float* __restrict__ partial) {
     constexpr int KS = L / 4;             // code steps of the decode
     constexpr int CT = (L + 15) / 16;     // code tiles of the gradient
@@ -192,7 +228,7 @@ __global__ void __launch_bounds__(256) sem_loss_kernel(const float* __restrict__
             if (mt + 1 < MT) cur = nxt;
         }
     }
-    const int n = *count;
+    const int n = valid_total(V, counts, P);
     const float fn = (float)(n > 0 ? n : 1);
     float k1[NP], k2[NP], k3[NP], lj[NP];
     bool live[NP];
@@ -304,15 +340,243 @@ __global__ void __launch_bounds__(256) sem_loss_kernel(const float* __restrict__
     if (t == 0) partial[blockIdx.x] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
 }
 
+// The same with every target read once, for up to 64 tiles of 16 columns (D <=
+// 1024): a workgroup takes 32 pixels and holds their targets and decoded values
+// in registers between the sums and the gradient, its NW wavefronts splitting
+// the column tiles (at most four each: q, q + NW, ...).  The per-pixel sums and
+// the gradient's partial products meet in LDS, in wavefront order, and one
+// wavefront forms the pixels' coefficients.  Pixel 2 lo + j is column lo of pixel
+// tile j, so a lane's two tiles come in one 8-byte load.  A block without a valid
+// pixel reads no targets.
+//
+// What bounds it: latency and issue together.  640 x 480 x 512 under a mask of
+// two thirds reads 420 MB, 83 us for a kernel that only loads so; the matrix
+// products are 48 us and the arithmetic 65.  The registers are the stage and leave
+// two workgroups a CU, so E's operands (L <= 16, where they fit) are asked for
+// before the targets and before the barriers: asked for at their use, eight waits
+// for L2 a block made 200 us of the 182.  Two reads and two decodes of every
+// target (the kernel above) took 302.
+constexpr int SEM_REG_PIX = 32;
+constexpr int SEM_REG_TILES = 4;   // column tiles of a wavefront
+
+template <class T>
+__device__ __forceinline__ const T* lane_at(const float* base, uint32_t bytes) {
+    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+
+template <int L, int NW>
+__global__ void __launch_bounds__(64 * NW) sem_loss_regs_kernel(const float* __restrict__ wmap, int64_t P, int D,
+                                                               const float* __restrict__ E,
+                                                               const float* __restrict__ Gs,
+                                                               const uint8_t* __restrict__ V, float lambda,
+                                                               const int* __restrict__ counts,
+                                                               float* __restrict__ d_out,
+                                                               float* __restrict__ partial) {
+    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int KS = L / 4;             // code steps of the decode
+    constexpr int CT = (L + 15) / 16;     // code tiles of the gradient
+    constexpr int NT = SEM_REG_TILES, PIX = SEM_REG_PIX;
+    constexpr bool HELD = L <= 16;        // E's operands are asked for ahead of their use
+    __shared__ f32x4_t sums[NW][PIX], coef[PIX];
+    __shared__ __align__(16) float red[NW][16][PIX];  // one code tile's partial gradients
+    const int t = threadIdx.x, lane = t & 63, hi = lane >> 4, lo = lane & 15;
+    const int q = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t p0 = (int64_t)blockIdx.x * PIX;
+    const bool full = p0 + PIX <= P;
+    const int64_t pa = min(p0 + 2 * lo, P - 1), pb = min(p0 + 2 * lo + 1, P - 1);
+    // every wavefront sees the same 32 pixels: the branch is the workgroup's
+    const uint64_t even = __ballot(p0 + 2 * lo < P && (V == nullptr || V[pa] != 0));
+    const uint64_t odd = __ballot(p0 + 2 * lo + 1 < P && (V == nullptr || V[pb] != 0));
+    auto zero_out = [&](int c0, int c1) {
+        for (int o = t; o < (c1 - c0) * PIX; o += 64 * NW) {
+            const int64_t p = p0 + o % PIX;
+            if (p < P) d_out[(size_t)(c0 + o / PIX) * P + p] = 0.f;
+        }
+    };
+    if ((even | odd) == 0) {
+        zero_out(0, 4 + L);
+        if (t == 0) partial[blockIdx.x] = 0.f;
+        return;
+    }
+    const int MT = (D + 15) / 16;
+    // WHOLE: no pixel or column out of range, 32-bit lane offsets in the target rows
+    auto body = [&](auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        // the lane's two pixels of row 4 hi + r of a plane group (the group's first row is uniform)
+        const uint32_t off = ((uint32_t)(WHOLE ? 4 * hi * P : 0) + 2 * lo) * 4u;
+        auto pair = [&](const float* plane) { return f2u{plane[pa], plane[pb]}; };
+        // the decode's A values of a tile (E^T), and the gradient's: E[16 c + lo][16 mt + 4 hi .. + 3]
+        auto load_ea = [&](int mt, float (&ea)[KS]) {
+            const int d = 16 * mt + lo;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                if constexpr (WHOLE) ea[k] = *lane_at<float>(E + (size_t)(4 * k) * D + 16 * mt, (hi * D + lo) * 4u);
+                else ea[k] = d < D ? E[(size_t)(4 * k + hi) * D + d] : 0.f;
+            }
+        };
+        auto load_ec = [&](int mt, f4u (&ec)[CT]) {
+            const int d4 = 16 * mt + 4 * hi;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                if constexpr (WHOLE && L % 16 == 0)
+                    ec[c] = *lane_at<f4u>(E + (size_t)(16 * c) * D + 16 * mt, (lo * D + 4 * hi) * 4u);
+                else
+                    ec[c] = (16 * c + lo < L && d4 < D) ? *reinterpret_cast<const f4u*>(E + (size_t)(16 * c + lo) * D + d4)
+                                                        : f4u{0.f, 0.f, 0.f, 0.f};
+            }
+        };
+        // a wavefront without its last tile loads the last one there is, and leaves it unused
+        auto tile = [&](int i) { return min(q + NW * i, MT - 1); };
+        float wb[2][KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const float* row = wmap + (size_t)(4 + 4 * k + hi) * P;
+            const f2u w = WHOLE ? *reinterpret_cast<const f2u*>(row + p0 + 2 * lo) : pair(row);
+            wb[0][k] = w[0];
+            wb[1][k] = w[1];
+        }
+        float ea[HELD ? NT : 1][KS];
+        if constexpr (HELD)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) load_ea(tile(i), ea[i]);
+        f2u b[NT][4];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int d0 = 16 * tile(i);  // D % 4 == 0: a lane's four rows are all in or all out
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (WHOLE) b[i][r] = *lane_at<f2u>(Gs + (size_t)(d0 + r) * P + p0, off);
+                else b[i][r] = d0 + 4 * hi < D ? pair(Gs + (size_t)(d0 + 4 * hi + r) * P) : f2u{0.f, 0.f};
+            }
+        }
+        zero_out(0, 4);
+        f32x4_t f[NT][2];
+        float s4[2][4] = {};
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            if (q + NW * i >= MT) break;  // uniform
+            if constexpr (!HELD) load_ea(q + NW * i, ea[0]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                f[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < KS; ++k)
+                    f[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[HELD ? i : 0][k], wb[j][k], f[i][j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float fv = f[i][j][r], bv = b[i][r][j];
+                    s4[j][0] += fv * bv;
+                    s4[j][1] += fv * fv;
+                    s4[j][2] += bv * bv;
+                    s4[j][3] += fabsf(fv - bv);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float x, y;
+                xlane_swap<32>(s4[j][k], s4[j][k], x, y);
+                s4[j][k] = x + y;
+                xlane_swap<16>(s4[j][k], s4[j][k], x, y);
+                s4[j][k] = x + y;
+            }
+            if (hi == 0) sums[q][2 * lo + j] = f32x4_t{s4[j][0], s4[j][1], s4[j][2], s4[j][3]};
+        }
+        f4u ec[HELD ? NT : 1][CT];
+        if constexpr (HELD)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) load_ec(tile(i), ec[i]);
+        __syncthreads();
+        if (q == (int)(blockIdx.x % NW)) {
+            // one wavefront forms the pixels' coefficients, a pixel per lane (twice)
+            const int px = lane & 31, n = valid_total(V, counts, P);
+            const float fn = (float)(n > 0 ? n : 1);
+            f32x4_t s = sums[0][px];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) s += sums[w][px];
+            const float prod = sqrtf(s[1]) * sqrtf(s[2]);
+            const float den = fmaxf(prod, kCosEps);
+            const float cosv = s[0] / den;
+            // g_d = k1 b_d + k2 a_d + k3 sign(a_d - b_d)
+            const bool live = ((px & 1 ? odd : even) >> (px >> 1) & 1) != 0 && n > 0;
+            f32x4_t k;
+            k[0] = live ? -lambda / (fn * den) : 0.f;
+            k[1] = (live && prod > kCosEps && s[1] > 0.f) ? lambda * cosv / (fn * s[1]) : 0.f;
+            k[2] = live ? lambda / (fn * (float)D) : 0.f;
+            k[3] = 0.f;
+            if (lane < PIX) coef[px] = k;
+            // the block's share of the loss, a fixed tree
+            float v = live && lane < PIX ? lambda * ((1.f - cosv) / fn + s[3] / (fn * (float)D)) : 0.f;
+            v = wave_sum(v);
+            if (lane == 0) partial[blockIdx.x] = v;
+        }
+        __syncthreads();
+        float k1[2], k2[2], k3[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const f32x4_t k = coef[2 * lo + j];
+            k1[j] = k[0];
+            k2[j] = k[1];
+            k3[j] = k[2] * 0x1p22f;  // exact, as is the product with +-2^-22 below
+        }
+        f32x4_t acc[2][CT];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[j][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            if (q + NW * i >= MT) break;
+            if constexpr (!HELD) load_ec(q + NW * i, ec[0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    // sign of the difference times 2^-22, which is 2^127 times the smallest float
+                    const float df = f[i][j][r] - b[i][r][j];
+                    const float sg = __builtin_amdgcn_fmed3f(df * 0x1p127f, -0x1p-22f, 0x1p-22f);
+                    const float gd = k1[j] * b[i][r][j] + k2[j] * f[i][j][r] + k3[j] * sg;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        acc[j][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ec[HELD ? i : 0][c][r], gd, acc[j][c], 0, 0, 0);
+                }
+        }
+        // acc[j][c][r]: code 16 c + 4 hi + r, pixel 2 lo + j; one code tile at a time
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            if (c > 0) __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<f2u*>(&red[q][4 * hi + r][2 * lo]) = f2u{acc[0][c][r], acc[1][c][r]};
+            __syncthreads();
+            for (int o = t; o < 16 * PIX; o += 64 * NW) {
+                const int code = o / PIX, px = o % PIX;
+                float v = red[0][code][px];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) v += red[w][code][px];
+                if (16 * c + code < L && (WHOLE || p0 + px < P)) d_out[(size_t)(4 + 16 * c + code) * P + p0 + px] = v;
+            }
+        }
+    };
+    if (full && D % 16 == 0 && P < (int64_t)1 << 26) body(std::true_type{});
+    else body(std::false_type{});
+}
+
 // Sums the per-workgroup losses in a fixed order.
-__global__ void __launch_bounds__(256) sem_loss_total_kernel(const float* __restrict__ partial, int nb,
-                                                            float* __restrict__ loss) {
-    __shared__ float r[256];
+__global__ void __launch_bounds__(1024) sem_loss_total_kernel(const float* __restrict__ partial, int nb,
+                                                             float* __restrict__ loss) {
+    __shared__ float r[1024];
     float s = 0.f;
-    for (int i = threadIdx.x; i < nb; i += 256) s += partial[i];
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nb; i += 1024) s += partial[i];
     r[threadIdx.x] = s;
     __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
+    for (int o = 512; o >= 1; o >>= 1) {
         if (threadIdx.x < o) r[threadIdx.x] += r[threadIdx.x + o];
         __syncthreads();
     }
@@ -362,13 +626,32 @@ extern "C" xgs_status xgs_semantic_softmax_bwd(const float* w, const float* dw, 
     return check_launch("xgs_semantic_softmax_bwd");
 }
 
-static size_t sem_blocks(int64_t P) { return (size_t)((P + SEM_PIX - 1) / SEM_PIX); }
+// Workgroups of the two forms: the one that holds its targets in registers takes
+// up to 64 column tiles (four a wavefront, 16 wavefronts), the other what is beyond,
+// and calls whose workspace holds only the other's partial losses.
+static size_t sem_blocks(int64_t P, int pix) { return (size_t)((P + pix - 1) / pix); }
+constexpr int kSemRegsMaxD = 16 * 16 * SEM_REG_TILES;
+
+template <int L>
+static void launch_sem_regs(int64_t P, int D, const float* wmap, const float* E, const float* Gs, const uint8_t* V,
+                            float lambda, const int* counts, float* d_out, float* partial, hipStream_t st) {
+    const dim3 nb((unsigned)sem_blocks(P, SEM_REG_PIX));
+    auto launch = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, nb, dim3(64 * waves), 0, st, wmap, P, D, E, Gs, V, lambda, counts, d_out, partial);
+    };
+    const int waves = ((D + 15) / 16 + SEM_REG_TILES - 1) / SEM_REG_TILES;
+    if (waves <= 1) launch(sem_loss_regs_kernel<L, 1>, 1);
+    else if (waves <= 2) launch(sem_loss_regs_kernel<L, 2>, 2);
+    else if (waves <= 4) launch(sem_loss_regs_kernel<L, 4>, 4);
+    else if (waves <= 8) launch(sem_loss_regs_kernel<L, 8>, 8);
+    else launch(sem_loss_regs_kernel<L, 16>, 16);
+}
 
 extern "C" size_t xgs_semantic_loss_workspace(int32_t Hs, int32_t Ws) {
     if (Hs < 1 || Ws < 1) return 0;
     Carve c(nullptr);
-    c.take<int>(1);
-    c.take<float>(sem_blocks((int64_t)Hs * Ws));
+    c.take<int>(kCountBlocks);
+    c.take<float>(sem_blocks((int64_t)Hs * Ws, SEM_REG_PIX));
     return c.total();
 }
 
@@ -385,23 +668,25 @@ extern "C" xgs_status xgs_semantic_loss(const float* wmap, int32_t L, int32_t Hs
     if (!aligned(ws, 256)) return fail(XGS_ERR_INVALID_ARG, "xgs_semantic_loss: workspace must be 256-byte aligned");
     const int64_t P = (int64_t)Hs * Ws;
     Carve c(ws);
-    int* count = c.take<int>(1);
-    float* partial = c.take<float>(sem_blocks(P));
+    int* counts = c.take<int>(kCountBlocks);
+    const size_t regs_bytes = [&] { Carve k = c; k.take<float>(sem_blocks(P, SEM_REG_PIX)); return k.total(); }();
+    float* partial = c.take<float>(sem_blocks(P, SEM_PIX));
     if (!ws || ws_bytes < c.total()) return fail(XGS_ERR_CAPACITY, "xgs_semantic_loss: workspace too small");
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(sem_zero_kernel, dim3(1), dim3(1), 0, st, count);
-    if (V) {
-        const unsigned g = (unsigned)std::min<int64_t>((P + 255) / 256, 1024);
-        hipLaunchKernelGGL(sem_count_kernel, dim3(g), dim3(256), 0, st, V, P, count);
-    } else {
-        hipLaunchKernelGGL(sem_fill_count_kernel, dim3(1), dim3(1), 0, st, count, (int)std::min<int64_t>(P, INT32_MAX));
-    }
-    const unsigned nb = (unsigned)sem_blocks(P);
-#define XGS_SL(LL)                                                                                             \
-    hipLaunchKernelGGL(sem_loss_kernel<LL>, dim3(nb), dim3(256), 0, st, wmap, P, D, E, Gstar, V, lambda, count, \
-                       d_out, partial)
-    XGS_SEM_DISPATCH(L, XGS_SL)
+    if (V) hipLaunchKernelGGL(sem_count_kernel, dim3(kCountBlocks), dim3(1024), 0, st, V, P, counts);
+    const bool regs = D <= kSemRegsMaxD && ws_bytes >= regs_bytes;
+    const unsigned nb = (unsigned)sem_blocks(P, regs ? SEM_REG_PIX : SEM_PIX);
+    if (regs) {
+#define XGS_SL(LL) launch_sem_regs<LL>(P, D, wmap, E, Gstar, V, lambda, counts, d_out, partial, st)
+        XGS_SEM_DISPATCH(L, XGS_SL)
 #undef XGS_SL
-    hipLaunchKernelGGL(sem_loss_total_kernel, dim3(1), dim3(256), 0, st, partial, (int)nb, loss);
+    } else {
+#define XGS_SL(LL)                                                                                              \
+    hipLaunchKernelGGL(sem_loss_kernel<LL>, dim3(nb), dim3(256), 0, st, wmap, P, D, E, Gstar, V, lambda, counts, \
+                       d_out, partial)
+        XGS_SEM_DISPATCH(L, XGS_SL)
+#undef XGS_SL
+    }
+    hipLaunchKernelGGL(sem_loss_total_kernel, dim3(1), dim3(1024), 0, st, partial, (int)nb, loss);
     return check_launch("xgs_semantic_loss");
 }
