@@ -401,7 +401,7 @@ xgs_status xgs_occluder_mask(const xgs_projected* p, int64_t n, const float* dep
 
 /* ------------------------------------------------------ a6: VQ assignment
  * a_n = argmin_l ||x_n - E_l||^2 (Sec. 3.2.2), ties to the lowest l.
- * XGS_VQ_FP32: direct FP32 sum of (x - e)^2 over every codeword.
+ * XGS_VQ_FP32: smallest direct FP32 sum of (x - e)^2 over every codeword.
  * XGS_VQ_BF16_RESCORE4: the squared distances of the bf16 roundings x^, e^
  * are formed on MFMA (FP32 accumulation, the norms folded into the product)
  * and each row keeps its 4 best codewords, ranked by half that distance with
