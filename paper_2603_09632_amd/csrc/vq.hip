@@ -1484,12 +1484,11 @@ constexpr int EMA_COLS = 4, EMA_ROWS = 8;
 // workgroup behind.
 constexpr int EMA_PIECE = 128;
 
-// One workgroup: the pieces of each code (ceil(n_l / P) for its n_l rows) and
-// their exclusive prefix poff[0..K]; each thread takes a contiguous run of
+// One workgroup of 1,024: the pieces of each code (ceil(n_l / P) for its n_l rows)
+// and their exclusive prefix poff[0..K]; each thread takes a contiguous run of
 // codes, so the pieces of a code are consecutive and in row order.
-__global__ void __launch_bounds__(1024) ema_pieces_kernel(const uint32_t* __restrict__ ranges, int K,
-                                                         uint32_t* __restrict__ poff) {
-    __shared__ uint32_t part[1024];
+__device__ __forceinline__ void ema_count_pieces(uint32_t (&part)[1024], const uint32_t* ranges, int K,
+                                                 uint32_t* __restrict__ poff) {
     const int t = threadIdx.x;
     const int per = (K + 1023) / 1024;
     const int k0 = min(K, t * per), k1 = min(K, k0 + per);
@@ -1509,6 +1508,63 @@ __global__ void __launch_bounds__(1024) ema_pieces_kernel(const uint32_t* __rest
         run += (ranges[2 * k + 1] - ranges[2 * k] + EMA_PIECE - 1) / EMA_PIECE;
     }
     if (t == 1023) poff[K] = part[1023];
+}
+
+__global__ void __launch_bounds__(1024) ema_pieces_kernel(const uint32_t* __restrict__ ranges, int K,
+                                                         uint32_t* __restrict__ poff) {
+    __shared__ uint32_t part[1024];
+    ema_count_pieces(part, ranges, K, poff);
+}
+
+// Few rows: one workgroup does what the key, sort, range and piece kernels do, with
+// the same rows, ranges and pieces.  Keys code << 12 | row are distinct, so a
+// bitonic sort in LDS orders the rows of a code as the stable sort does; steps
+// across at most 64 elements stay within a wavefront's 128 and need no barrier.
+// What bounds it: the chain of steps (66 for 2,048 elements).  1,200 rows, 4,096
+// codes: eight launches of 52 us become one of 22.
+constexpr int EMA_FEW_BITS = 11, EMA_FEW_ROWS = 1 << EMA_FEW_BITS, EMA_FEW_CODES = 1 << 14;
+
+__global__ void __launch_bounds__(1024) ema_few_kernel(const int32_t* __restrict__ idx, int N, int K,
+                                                      const float* __restrict__ conf, float gamma, int size,
+                                                      uint32_t* __restrict__ rows, uint32_t* ranges,
+                                                      uint32_t* __restrict__ poff) {
+    __shared__ uint32_t key[EMA_FEW_ROWS];
+    __shared__ uint32_t part[1024];
+    const int t = threadIdx.x;
+    for (int n = t; n < size; n += 1024) {
+        uint32_t k = 0xFFFFFFFFu;
+        if (n < N) {
+            int a = idx[n];
+            a = a < 0 ? 0 : (a >= K ? K - 1 : a);
+            if (conf && !(conf[n] >= gamma)) a = K;
+            k = (uint32_t)a << EMA_FEW_BITS | (uint32_t)n;
+        }
+        key[n] = k;
+    }
+    for (int k = t; k < 2 * (K + 1); k += 1024) ranges[k] = 0u;
+    __syncthreads();
+    for (int k = 2; k <= size; k <<= 1)
+        for (int j = k >> 1; j >= 1; j >>= 1) {
+            for (int p = t; p < size / 2; p += 1024) {
+                const int a = 2 * p - (p & (j - 1)), b = a + j;
+                const uint32_t x = key[a], y = key[b];
+                const bool up = (a & k) == 0;
+                key[a] = up ? min(x, y) : max(x, y);
+                key[b] = up ? max(x, y) : min(x, y);
+            }
+            // the next step's stride: j / 2, or k after the last of a merge
+            if (j > 64 || (j == 1 && k > 64)) __syncthreads();
+            else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    __syncthreads();
+    for (int n = t; n < N; n += 1024) {
+        const uint32_t k = key[n], c = k >> EMA_FEW_BITS;
+        rows[n] = k & (EMA_FEW_ROWS - 1);
+        if (n == 0 || key[n - 1] >> EMA_FEW_BITS != c) ranges[2 * c] = (uint32_t)n;
+        if (n == N - 1 || key[n + 1] >> EMA_FEW_BITS != c) ranges[2 * c + 1] = (uint32_t)n + 1;
+    }
+    __syncthreads();
+    ema_count_pieces(part, ranges, K, poff);
 }
 
 // One workgroup per piece: the column sums of its (at most P) rows, added in
@@ -1564,7 +1620,9 @@ __global__ void __launch_bounds__(256) ema_piece_sum_kernel(const float* __restr
 
 // One workgroup per code: the code's sum is its pieces' sums added in piece
 // order (fixed by the row counts alone, so the result is reproducible), then
-// the EMA step of Eq. (ema_update) on N and M.
+// the EMA step of Eq. (ema_update) on N and M.  Eight pieces are loaded before
+// they are added: one by one, the code with the most pieces left a chain of memory
+// latencies (816,000 rows on 4,096 codes, 119 us; 22 so).
 __global__ void __launch_bounds__(256) ema_combine_kernel(const float* __restrict__ partial, int D,
                                                          const uint32_t* __restrict__ ranges,
                                                          const uint32_t* __restrict__ poff, float decay,
@@ -1572,11 +1630,31 @@ __global__ void __launch_bounds__(256) ema_combine_kernel(const float* __restric
                                                          float* __restrict__ counts) {
     const int l = blockIdx.x, t = threadIdx.x;
     const uint32_t p0 = poff[l], p1 = poff[l + 1];
-    for (int d = t; d < D; d += 256) {
-        float acc = 0.f;
-        for (uint32_t q = p0; q < p1; ++q) acc += partial[(size_t)q * D + d];
-        float* m = M_ema + (size_t)l * D + d;
-        *m = decay * *m + (1.f - decay) * acc;
+    for (int d0 = 0; d0 < D; d0 += 256 * EMA_COLS) {
+        float* m = M_ema + (size_t)l * D + d0 + t;
+        float old[EMA_COLS], acc[EMA_COLS];
+#pragma unroll
+        for (int c = 0; c < EMA_COLS; ++c) {
+            old[c] = d0 + t + 256 * c < D ? m[256 * c] : 0.f;
+            acc[c] = 0.f;
+        }
+        for (uint32_t q = p0; q < p1; q += EMA_ROWS) {
+            float v[EMA_ROWS][EMA_COLS];
+#pragma unroll
+            for (int j = 0; j < EMA_ROWS; ++j)
+#pragma unroll
+                for (int c = 0; c < EMA_COLS; ++c) {
+                    const int d = d0 + t + 256 * c;
+                    v[j][c] = q + j < p1 && d < D ? partial[(size_t)(q + j) * D + d] : 0.f;
+                }
+#pragma unroll
+            for (int j = 0; j < EMA_ROWS; ++j)
+#pragma unroll
+                for (int c = 0; c < EMA_COLS; ++c) acc[c] += v[j][c];
+        }
+#pragma unroll
+        for (int c = 0; c < EMA_COLS; ++c)
+            if (d0 + t + 256 * c < D) m[256 * c] = fmaf(1.f - decay, acc[c], decay * old[c]);
     }
     if (t == 0) {
         const float c = (float)(ranges[2 * l + 1] - ranges[2 * l]);
@@ -1863,18 +1941,29 @@ static xgs_status ema_impl(const char* who, const float* X, const int32_t* idx, 
     EmaWs w = carve_ema(ws, N, D, K, &need);
     if (!ws || ws_bytes < need) return fail(XGS_ERR_CAPACITY, w_ + ": workspace too small");
     xgs_status s;
-    if ((s = fill_u32(w.ranges, 2 * ((int64_t)K + 1), 0u, st))) return s;
-    const int64_t n1 = N > 0 ? N : 1;
-    hipLaunchKernelGGL(ema_keys_kernel, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, st, idx, N, K, conf, gamma,
-                       w.keys, w.vals, w.count);
-    if ((s = check_launch(who))) return s;
-    const int bits = bits_for((int64_t)K + 1);
-    if ((s = radix_sort(w.keys, w.vals, w.keys_alt, w.vals_alt, w.count, N, bits, w.hist, st))) return s;
-    const bool even = radix_passes(bits, N) % 2 == 0;
-    const uint64_t* sk = even ? w.keys : w.keys_alt;
-    const uint32_t* sv = even ? w.vals : w.vals_alt;
-    if ((s = segment_ranges(sk, w.count, N, 0, w.ranges, st))) return s;
-    hipLaunchKernelGGL(ema_pieces_kernel, dim3(1), dim3(1024), 0, st, w.ranges, K, w.poff);
+    const uint32_t* sv = w.vals;  // rows by code
+    // one workgroup's sort of up to 2,048 rows; whole updates, D = 64 and 768: 300 rows on
+    // 64 codes 22 us (general 39), 1,200 on 4,096 43 (60), 2,048 on 64 34 (39); 4,096 on 64
+    // would be 50 (44, one radix pass)
+    if (N <= EMA_FEW_ROWS && K <= EMA_FEW_CODES) {
+        int size = 2;
+        while (size < N) size <<= 1;
+        hipLaunchKernelGGL(ema_few_kernel, dim3(1), dim3(1024), 0, st, idx, (int)N, K, conf, gamma, size, w.vals,
+                           w.ranges, w.poff);
+    } else {
+        if ((s = fill_u32(w.ranges, 2 * ((int64_t)K + 1), 0u, st))) return s;
+        const int64_t n1 = N > 0 ? N : 1;
+        hipLaunchKernelGGL(ema_keys_kernel, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, st, idx, N, K, conf,
+                           gamma, w.keys, w.vals, w.count);
+        if ((s = check_launch(who))) return s;
+        const int bits = bits_for((int64_t)K + 1);
+        if ((s = radix_sort(w.keys, w.vals, w.keys_alt, w.vals_alt, w.count, N, bits, w.hist, st))) return s;
+        const bool even = radix_passes(bits, N) % 2 == 0;
+        const uint64_t* sk = even ? w.keys : w.keys_alt;
+        if (!even) sv = w.vals_alt;
+        if ((s = segment_ranges(sk, w.count, N, 0, w.ranges, st))) return s;
+        hipLaunchKernelGGL(ema_pieces_kernel, dim3(1), dim3(1024), 0, st, w.ranges, K, w.poff);
+    }
     hipLaunchKernelGGL(ema_piece_sum_kernel, dim3((unsigned)ema_max_pieces(N, K)), dim3(256), 0, st, X, D, sv,
                        w.ranges, w.poff, K, w.partial);
     hipLaunchKernelGGL(ema_combine_kernel, dim3((unsigned)K), dim3(256), 0, st, w.partial, D, w.ranges, w.poff,
@@ -1886,7 +1975,8 @@ static xgs_status ema_impl(const char* who, const float* X, const int32_t* idx, 
     } else if (n_dead) {
         hipLaunchKernelGGL(ema_zero_i32_kernel, dim3(1), dim3(1), 0, st, n_dead);
     }
-    hipLaunchKernelGGL(ema_total_kernel, dim3(1), dim3(256), 0, st, N_ema, K, w.total);
+    if (mode != XGS_EMA_PAPER)
+        hipLaunchKernelGGL(ema_total_kernel, dim3(1), dim3(256), 0, st, N_ema, K, w.total);
     hipLaunchKernelGGL(ema_finalize_kernel, dim3((unsigned)K), dim3(256), 0, st, N_ema, M_ema, K, D, eps, mode,
                        w.total, E, E_bf16, e_norm2);
     return check_launch(who);
