@@ -26,8 +26,10 @@ class RenderFunction(torch.autograd.Function):
                       colors.contiguous(), features.contiguous())
         c = camera_from(cam)
         p = xgs_project(g, c)
-        if max_instances is None:
-            max_instances = int(p.tiles_touched.to(torch.int64).sum().item())
+        # a capacity counted here holds every instance; the caller's may not
+        ctx.counted = max_instances is None
+        if ctx.counted:
+            max_instances = int(p.tiles_touched.sum(dtype=torch.int64).item())
         b = alloc_binning(g.n, max(int(max_instances), 1), c, means.device)
         xgs_tile_sort(p, c, g.n, b)
         out, final_T, n_last = xgs_render_fwd(g, p, b, c)
@@ -44,7 +46,10 @@ class RenderFunction(torch.autograd.Function):
     def backward(ctx, d_out, _d_final_T, _d_n_last):
         (means, log_scales, quats, opacity, colors, features, splat, radius, tile_rect, touched, keys, vals,
          ranges, num_inst, status, tile_order, final_T, n_last) = ctx.saved_tensors
-        if int(status.item()) != 0:
+        # Reading the status waits for the forward pass, which leaves the GPU idle
+        # while the host enqueues the backward: only where it can be set (640 x 480,
+        # 300k Gaussians, forward and backward: 319 us with the wait, 296 without).
+        if not ctx.counted and int(status.item()) != 0:
             raise XgsError("render: the instance buffers overflowed in the forward pass")
         g = Gaussians(means, log_scales, quats, opacity, colors, features)
         p = Projected(splat, radius, tile_rect, touched)
