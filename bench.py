@@ -456,7 +456,7 @@ def semantic_phase(xgs, synth, dev, G, reps: int = 10):
     torch.cuda.synchronize()
     ms = {n: float(np.mean([e[i].elapsed_time(e[i + 1]) for e in evs_all])) for i, n in enumerate(names)}
     P_ = 480 * 640
-    loss_bytes = 2 * D * P_ * 4 + L * P_ * 4 + P_ + (4 + L) * P_ * 4
+    loss_bytes = D * P_ * 4 + L * P_ * 4 + P_ + (4 + L) * P_ * 4
     return {"workload": "300k-Gaussian room, 640x480, L=16 mixture weights, D=512 targets, geometry frozen",
             "ms": {k: round(v, 4) for k, v in ms.items()}, "total_ms": round(sum(ms.values()), 4),
             "instances": m, "loss": float(loss.item()),
