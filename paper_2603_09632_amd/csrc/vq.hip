@@ -1268,69 +1268,41 @@ __global__ void __launch_bounds__(256) vq_rescore_kernel(const float* __restrict
     }
 }
 
-// Rescore with four rows per wavefront, for D % 4 == 0: lanes 16 r .. 16 r + 15
-// hold the candidates of row r (one each for up to 4 parts; FEW: the four of a
-// part, which are stored best last, for up to 16), so each of the four selection
-// rounds is one 4-step butterfly within rows of 16 lanes serving all four rows;
-// the 16 FP32 distances (4 rows x 4 picks) are summed by one reduce-scatter
-// instead of 16 full wavefront sums.
-// Same candidates, same picks and the same per-lane partial sums as the
-// one-row form; only the order of the final cross-lane additions differs.
-// FEW with split (few rows, long enough for their loads to matter): the four wavefronts of a
-// workgroup take one of its four rows each, with the same sums (the other rows'
-// stay zero), where one wavefront's chain of loads would be the time.  Whole
-// assignments against 4,096 codewords, by fours and split: 300 x 768 57 and 46 us,
-// 4,800 x 768 90 and 82, 8,192 x 384 78 and 73; 1,200 x 128 39 and 45, 33,000 x 256
-// (2,048 codewords) 114 and 123.
-constexpr int64_t VQ_SPLIT_ROWS = 8192;
-constexpr int VQ_SPLIT_D = 384;
-
-template <bool CONF, bool FEW>
+// Rescore with four rows per wavefront, for up to 16 candidates per row
+// (parts <= 4) and D % 4 == 0: lanes 16 r .. 16 r + 15 hold the candidates of
+// row r, so each of the four selection rounds is one 4-step butterfly within
+// rows of 16 lanes serving all four rows; the 16 FP32 distances (4 rows x 4
+// picks) are summed by one reduce-scatter instead of 16 full wavefront sums.
+// Same candidates, same picks, same per-lane partial sums and the same pairs of
+// lanes in the cross-lane additions as the one-row form: the same bits.
+template <bool CONF>
 __global__ void __launch_bounds__(256) vq_rescore4_kernel(const float* __restrict__ X, int64_t N, int D,
                                                          const float* __restrict__ E,
                                                          const int2* __restrict__ cand, int parts,
                                                          int32_t* __restrict__ idx, float* __restrict__ dist,
                                                          const float2* __restrict__ lse,
-                                                         float* __restrict__ conf, bool split_) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool split = FEW && split_;
-    const int64_t row0 = split ? (int64_t)blockIdx.x * 4 : ((int64_t)blockIdx.x * 4 + wave) * 4;
+                                                         float* __restrict__ conf) {
+    const int lane = threadIdx.x & 63;
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 4;
     if (row0 >= N) return;  // uniform per wave
     const int grp = lane >> 4, j = lane & 15;
     const int64_t myrow = row0 + grp;
-    int4 c01 = make_int4(0x7FFFFFFF, -1, 0x7FFFFFFF, -1), c23 = c01;
-    if constexpr (FEW) {
-        if (j < parts && myrow < N) {
-            const int4* c = reinterpret_cast<const int4*>(cand + (myrow * parts + j) * 4);
-            const int4 a = c[0], b = c[1];
-            c01 = make_int4(b.z, b.w, b.x, b.y);
-            c23 = make_int4(a.z, a.w, a.x, a.y);
-        }
-    } else if (j < 4 * parts && myrow < N) {
-        const int2 v = cand[myrow * (4 * parts) + j];
-        c01.x = v.x;
-        c01.y = v.y;
-    }
+    const int nc = 4 * parts;
+    const int2 v = (j < nc && myrow < N) ? cand[myrow * nc + j] : make_int2(0x7FFFFFFF, -1);
+    int ck = v.x, cc = v.y;
     int pk[4];
     auto take = [&](int& bk, int& bc, int ok, int oc) {
         if (cand_before(ok, oc, bk, bc)) { bk = ok; bc = oc; }
     };
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        int bk = c01.x, bc = c01.y;
+        int bk = ck, bc = cc;
         take(bk, bc, xlane_partner<8>(bk, lane), xlane_partner<8>(bc, lane));
         take(bk, bc, xlane_partner<4>(bk, lane), xlane_partner<4>(bc, lane));
         take(bk, bc, xlane_partner<2>(bk, lane), xlane_partner<2>(bc, lane));
         take(bk, bc, xlane_partner<1>(bk, lane), xlane_partner<1>(bc, lane));
         pk[q] = bc;
-        if (c01.y == bc) {  // codewords are distinct across lists
-            if constexpr (FEW) {
-                c01 = make_int4(c01.z, c01.w, c23.x, c23.y);
-                c23 = make_int4(c23.z, c23.w, 0x7FFFFFFF, -1);
-            } else {
-                c01.y = -1;
-            }
-        }
+        if (cc == bc) cc = -1;  // codewords are distinct across lists
     }
     int pick[4][4];
 #pragma unroll
@@ -1344,7 +1316,6 @@ __global__ void __launch_bounds__(256) vq_rescore4_kernel(const float* __restric
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         if (row0 + r >= N) break;  // uniform
-        if (split && r != wave) continue;
         const f32x4_t* xr = reinterpret_cast<const f32x4_t*>(X + (row0 + r) * D);
         const f32x4_t* er[4];
 #pragma unroll
@@ -1378,7 +1349,6 @@ __global__ void __launch_bounds__(256) vq_rescore4_kernel(const float* __restric
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         if (row0 + r >= N) break;
-        if (split && r != wave) continue;
         float bd = INFINITY;
         int bi = 0x7FFFFFFF;
 #pragma unroll
@@ -1402,7 +1372,7 @@ __global__ void __launch_bounds__(256) vq_rescore4_kernel(const float* __restric
         sum += xlane_dpp<4>(sum);
         sum += xlane_dpp<2>(sum);
         sum += xlane_dpp<1>(sum);
-        if (j == 0 && myrow < N && (!split || grp == wave)) conf[myrow] = 1.f / sum;
+        if (j == 0 && myrow < N) conf[myrow] = 1.f / sum;
     }
 }
 
@@ -1415,7 +1385,6 @@ struct VqWs {
 
 struct VqPlan {
     int tiles, tiles_part, parts, seq_bits;
-    int rank_parts;  // parts by the number of codewords alone: those choose the rescore's form
 };
 
 static VqPlan vq_plan(int K) {
@@ -1430,7 +1399,6 @@ static VqPlan vq_plan(int K) {
     int b = 0;
     while ((1 << b) < p.tiles_part) ++b;
     p.seq_bits = 6 + b;
-    p.rank_parts = p.parts;
     return p;
 }
 
@@ -1440,8 +1408,8 @@ static int64_t vq_np(int64_t N) { return (N + VqCfg::ROWS - 1) / VqCfg::ROWS * V
 // The same plan in more parts where few row blocks leave CUs idle: up to a workgroup
 // for each of the 256.  Ranks keep their bits (seq_bits), and lists merge by rank,
 // then codeword, so the four candidates are the same in any number of parts.
-// Whole assignments with confidence, 4,096 x 768: 1,200 rows 119 us in 4 parts, 61 in
-// 16 (without 92 and 57), 4,800 rows 127 and 103 in 6.
+// Whole assignments with confidence, 4,096 x 768, with the one-row rescore: 1,200 rows
+// 106 us in 4 parts, 45 in 16; 4,800 rows 116 and 89 in 6.
 static VqPlan vq_plan_fine(int64_t N, int K) {
     VqPlan p = vq_plan(K);
     const int64_t blocks = std::max<int64_t>(1, (N + VqCfg::ROWS - 1) / VqCfg::ROWS);
@@ -1884,23 +1852,23 @@ extern "C" xgs_status xgs_vq_candidates(int64_t N, int32_t D, int32_t K, void* w
     return check_launch("xgs_vq_candidates");
 }
 
-// Four rows per wavefront for codebooks of at most 4 parts by their size (16,384
-// codewords) where the rows are float4-aligned; one row per wavefront otherwise.
+// Four rows per wavefront for many rows of at most 16 candidates that are
+// float4-aligned; one row per wavefront otherwise (the same bits).  The four-row form
+// shares its selection and sums between the rows, but is 30 KB of straight code
+// that few wavefronts run once.  Whole assignments by fours and by ones (us): 1,200 x
+// 768 on 1,024 53 and 39, 33,000 x 64 84 and 79, 50,000 x 128 117 and 113, 100,000 x
+// 128 191 and 196, 200,000 x 256 391 and 402; long rows hide more: 100,000 x 384 265
+// and 253, 200,000 x 768 751 and 732.
+static bool vq_few_rows(int64_t N, int D) { return N <= (D >= 384 ? 262144 : 65536); }
+
 template <bool CONF>
-static void launch_rescore(const float* X, int64_t N, int D, const float* E, int K, const int2* cand,
-                           const VqPlan& plan, int32_t* idx, float* dist, const float2* lse, float* conf,
-                           hipStream_t st) {
-    const int parts = plan.parts;
+static void launch_rescore(const float* X, int64_t N, int D, const float* E, int K, const int2* cand, int parts,
+                           int32_t* idx, float* dist, const float2* lse, float* conf, hipStream_t st) {
     const bool v4 = D % 4 == 0 && aligned(X, 16) && aligned(E, 16);
-    if (v4 && plan.rank_parts <= 4) {
-        const bool split = N <= VQ_SPLIT_ROWS && D >= VQ_SPLIT_D;
-        const unsigned blocks = (unsigned)((N + (split ? 3 : 15)) / (split ? 4 : 16));
-        auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, X, N, D, E, cand, parts, idx, dist, lse, conf,
-                               split);
-        };
-        if (split || parts > 4) launch(vq_rescore4_kernel<CONF, true>);
-        else launch(vq_rescore4_kernel<CONF, false>);
+    if (v4 && parts <= 4 && !vq_few_rows(N, D)) {
+        const unsigned blocks = (unsigned)((N + 15) / 16);
+        hipLaunchKernelGGL((vq_rescore4_kernel<CONF>), dim3(blocks), dim3(256), 0, st, X, N, D, E, cand, parts, idx,
+                           dist, lse, conf);
         return;
     }
     const unsigned blocks = (unsigned)((N + 3) / 4);
@@ -1920,7 +1888,7 @@ extern "C" xgs_status xgs_vq_rescore(const float* X, int64_t N, int32_t D, const
     if (xgs_status s = vq_bf16_setup("xgs_vq_rescore", N, D, K, ws, ws_bytes, &plan, &w)) return s;
     if (N == 0) return XGS_OK;
     if (!X || !E || !idx || !dist) return fail(XGS_ERR_INVALID_ARG, "xgs_vq_rescore: null pointer");
-    launch_rescore<false>(X, N, D, E, K, w.cand, plan, idx, dist, nullptr, nullptr, (hipStream_t)stream);
+    launch_rescore<false>(X, N, D, E, K, w.cand, plan.parts, idx, dist, nullptr, nullptr, (hipStream_t)stream);
     return check_launch("xgs_vq_rescore");
 }
 
@@ -1940,7 +1908,7 @@ extern "C" xgs_status xgs_vq_assign_conf(const float* X, int64_t N, int32_t D, c
     const int64_t gb = ((N + VqCfg::ROWS - 1) / VqCfg::ROWS + 7) / 8 * 8 * plan.parts;
     hipLaunchKernelGGL((vq_gemm_kernel<VqCfg, true>), dim3((unsigned)gb), dim3(VqCfg::THREADS), 0, st, w.xa, N, vq_dp(D) + Q_BK, w.ea, K,
                        plan.parts, plan.tiles_part, plan.seq_bits, w.cand, 1.f / tau, w.lse);
-    launch_rescore<true>(X, N, D, E, K, w.cand, plan, idx, dist, w.lse, conf, st);
+    launch_rescore<true>(X, N, D, E, K, w.cand, plan.parts, idx, dist, w.lse, conf, st);
     return check_launch("xgs_vq_assign_conf");
 }
 

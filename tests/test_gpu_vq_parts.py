@@ -39,3 +39,18 @@ def test_more_parts_same_answer(xgs, n, k, d):
     for a, b in zip(*out):
         np.testing.assert_array_equal(a, b)
     assert not np.isin(out[0][0], np.arange(k // 2, k // 2 + 300)).any()
+
+
+# row counts on either side of the line between one and four rows a wavefront: the
+# first rows of a longer call get the same bits as on their own
+@pytest.mark.parametrize("n,d", [(65_537, 64), (262_145, 384)])
+def test_rescore_forms_same_bits(xgs, n, d):
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X, E = torch.randn(n, d, device="cuda", generator=gen), torch.randn(600, d, device="cuda", generator=gen)
+    Eb, en = xgs.xgs_vq_prepare(E)
+    long = xgs.xgs_vq_assign_conf(X, E, Eb, en, 0.7) + xgs.xgs_vq_assign(X, E, Eb, en)
+    few = X[:n - 2].contiguous()
+    short = xgs.xgs_vq_assign_conf(few, E, Eb, en, 0.7) + xgs.xgs_vq_assign(few, E, Eb, en)
+    torch.cuda.synchronize()
+    for a, b in zip(long, short):
+        assert torch.equal(a[:n - 2], b)
