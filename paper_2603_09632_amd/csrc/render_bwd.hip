@@ -54,8 +54,9 @@ enum { GW_MX = 0, GW_MY = 1, GW_XX = 2, GW_XY = 3, GW_YY = 4, GW_1 = 5, GW_DEPTH
 //
 // A pixel takes the splats eight at a time: first the eight alphas, which do
 // not depend on each other (0 for a pair that does not contribute, which then
-// leaves T and S as they are without further selects), then the chain of T and
-// S.  With b = a / (1 - a): w = b T, h = b (T g.c - S), S += w g.c, T /= 1 - a.
+// leaves T and S as they are without further selects; its s and h are selected,
+// because an infinite channel or gradient makes S infinite), then the chain of T
+// and S.  With b = a / (1 - a): w = b T, h = b (T g.c - S), S += w g.c, T /= 1 - a.
 // The sums over the quadrant are formed in two steps.  Over the rows (lane
 // bits 3-5): h, h dy and h dy^2 of the eight splats, by a reduce-scatter that
 // halves the splats at each exchange, so that lanes 8 s .. 8 s + 7 end with
@@ -295,7 +296,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
                 w[u] = b * T;
                 if constexpr (GEO) {
                     const float s = ok[u] ? sd[u >> 2][u & 3] : 0.f;  // a colour may be infinite
-                    const float h = al[u] < kAlphaMax ? b * (T * s - S) : 0.f;
+                    // a pair without a part in the pixel has h = 0 also where S is not finite
+                    const float h = ok[u] && al[u] < kAlphaMax ? b * (T * s - S) : 0.f;
                     S += w[u] * s;
                     a[V * u] = h;
                     a[V * u + 1] = h * dy[u];
