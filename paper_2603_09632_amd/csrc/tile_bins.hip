@@ -182,16 +182,20 @@ __global__ void __launch_bounds__(kBinThreads) bin_scatter_kernel(
         tv[j] = k < hi ? totals[k] : 0u;
         off[j] = k < hi ? row[k] : 0u;
     }
-    uint64_t carry = 0;
-    uint32_t first[STEPS];
+    // The positions fit 32 bits wherever they are used, but the total that says
+    // so may not: 64 tiles of 2^26 instances each make 2^32.
+    uint64_t sum = 0;
+    uint32_t first[STEPS], carry = 0;
 #pragma unroll
     for (int j = 0; j < STEPS; ++j) {
         if (lo + 64 * j >= hi) break;  // uniform across the wavefront
         const uint32_t incl = wave_incl_scan(tv[j], lane);
-        first[j] = (uint32_t)carry + incl - tv[j];
+        first[j] = carry + incl - tv[j];
         carry += __builtin_amdgcn_readlane(incl, 63);
+        sum += tv[j];
     }
-    if (lane == 0) wtot[w] = carry;
+    sum = wave_sum_u64(sum, lane);
+    if (lane == 0) wtot[w] = sum;
     __syncthreads();
     uint64_t base = 0, total = 0;
 #pragma unroll
