@@ -189,8 +189,9 @@ xgs_status xgs_tile_sort(const xgs_projected* p, const xgs_camera* cam, int64_t 
  * xgs_tile_sort, without ws: the sort runs in a scratch array of
  * xgs_tile_sort_noalloc_max_bytes() bytes (68 MiB: n = 2M Gaussians with
  * max_instances = 4M fit) that the library holds on each GPU it runs on until
- * the process ends.  A call whose xgs_tile_sort_workspace(n, max_instances,
- * tiles) exceeds that size returns XGS_ERR_CAPACITY before any launch.  The
+ * the process ends.  A call whose radix form would need more than that returns
+ * XGS_ERR_CAPACITY before any launch (the binning form is taken where it fits
+ * too).  The
  * entry point calls no hipMalloc, hipFree or allocating library routine.
  * All calls on one GPU share its scratch (later calls overwrite it): calls
  * that overlap on one GPU (different streams or threads without ordering)

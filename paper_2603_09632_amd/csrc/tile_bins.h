@@ -18,12 +18,20 @@ constexpr int kBinMaxTiles = 16384;
 // to end (1,286 instances: 27 us against 16 with the workgroup form).
 constexpr int kBinWaveKeys = 256;
 constexpr int kBinBlockKeys = 2048;
+// Runs that the first pass of the merge makes one, and so the longest lists that
+// need no other (a list has at most 8,193 x 16,384 pairs, 129 of them); pairs that a workgroup of the merge sorts in LDS, and those
+// workgroups (one fills a CU).
+constexpr int kBinFan = 512;
+constexpr int kBinFanKeys = kBinFan * kBinBlockKeys;
+constexpr int kBinMergeKeys = 8192;
+constexpr int kBinMergeBlocks = 256;
+// Lists that are merged by ranks.
+constexpr int kBinRankKeys = 8 * kBinBlockKeys;
 // Workgroups that take the longer lists (six to a CU by their LDS).
 constexpr int kBinLongBlocks = 1536;
-// Above this many instances per tile (of the capacity) the radix form is used:
-// the merge of long lists grows with the square of their runs.  On 48 tiles,
-// this form against the radix form: 4,000 instances on each 60 / 86 us, 8,000
-// 90 / 97 us; 100,000 on one tile 203 / 82 us.
+// Above this many instances per tile (of the capacity) the radix form is used: it
+// has caught up.  On 48 tiles, this form against the radix form: 2,000 instances
+// on each 36 / 80 us, 4,000 59 / 84, 8,000 89 / 95.
 constexpr int64_t kBinMaxMeanList = 8192;
 
 struct BinPlan {
@@ -51,6 +59,7 @@ struct BinWs {
     uint32_t* totals;   // [tiles]
     uint2* runs;        // (tile, first position in its list) of the runs of lists above kBinBlockKeys
     uint32_t* n_runs;
+    uint64_t* merged;   // [cap] runs of kBinFanKeys pairs, where a list can be longer
 };
 
 // Carves the workspace; *bytes is what it takes.

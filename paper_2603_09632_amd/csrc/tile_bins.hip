@@ -1,7 +1,7 @@
 // a2, tile sort by binning: the (tile, Gaussian) instances are counted per
 // tile, dropped into their tile's segment and sorted there by (depth,
 // Gaussian).  Five launches: count, scan, scatter, sort, and a merge that only
-// lists above 2,048 instances need.
+// lists above 2,048 instances need (a second one above 1M).
 //
 // A radix sort over the 41-46 key bits moves every pair five or six times and
 // takes 19 dependent launches, whose latency alone was most of its time.  The
@@ -433,54 +433,220 @@ __global__ void __launch_bounds__(256) bin_sort_kernel(uint64_t* __restrict__ pa
     }
 }
 
-// The lists above kBinBlockKeys: a pair's place is its index in its own run
-// plus its rank in each of the list's other runs, found in LDS.  The work
-// grows with the square of a list's runs.
-__global__ void __launch_bounds__(256) bin_merge_kernel(const uint64_t* __restrict__ pairs,
-                                                       const uint32_t* __restrict__ ranges,
-                                                       const uint2* __restrict__ runs,
-                                                       const uint32_t* __restrict__ n_runs,
-                                                       uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    constexpr int PER = kBinBlockKeys / 256;
-    __shared__ uint64_t lds[kBinBlockKeys];
-    const int t = threadIdx.x;
-    const uint32_t nr = *n_runs;
-    for (uint32_t r = blockIdx.x; r < nr; r += gridDim.x) {
-        const uint32_t tile = runs[r].x, own = runs[r].y;
-        const uint32_t a = ranges[2 * tile], m = ranges[2 * tile + 1] - a;
-        const uint32_t mine = min(m - own, (uint32_t)kBinBlockKeys);
-        uint64_t k[PER];
-        uint32_t rank[PER];
+// Adds to b[] the number of the len ascending elements at(0), at(1), ... below
+// each of k[]: three probes a step and key, which do not wait for each other
+// (past the end they read the last element, which is not counted).
+template <int N, class At>
+__device__ __forceinline__ void count_below(uint32_t len, const uint64_t (&k)[N], uint32_t (&b)[N], At at) {
+    if (len == 0) return;
+    uint32_t p[N] = {};
+    for (uint32_t s = 1u << ((31 - __builtin_clz(len)) & ~1); s >= 1; s >>= 2) {
+        uint64_t v[N][3];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const uint32_t i = 256u * j + t;
-            k[j] = i < mine ? pairs[a + own + i] : ~0ull;
-            rank[j] = i;
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (uint32_t q = 0; q < 3; ++q) v[j][q] = at(min(p[j] + (q + 1) * s, len) - 1);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            uint32_t less = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < 3; ++q) less += p[j] + (q + 1) * s <= len && v[j][q] < k[j] ? s : 0u;
+            p[j] += less;
         }
-        for (uint32_t o = 0; o < m; o += kBinBlockKeys) {
-            if (o == own) continue;
-            const uint32_t len = min(m - o, (uint32_t)kBinBlockKeys);
-            __syncthreads();
+    }
 #pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const uint32_t i = 256u * j + t;
-                lds[i] = i < len ? pairs[a + o + i] : ~0ull;
+    for (int j = 0; j < N; ++j) b[j] += p[j];
+}
+
+// Sorts get(0 .. m - 1), m <= 1024 E, with a workgroup of 16 wavefronts; sink(position,
+// pair) receives them.
+template <int E, class Get, class Sink>
+__device__ __forceinline__ void sort_wide(uint64_t* lds, uint32_t m, Get get, Sink sink) {
+    const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6;
+    uint64_t k[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) k[e] = 1024 * e + t < m ? get(1024 * e + t) : ~0ull;
+    merge_runs<E, 2>(k, lane);
+#pragma unroll 1
+    for (uint32_t r = 2; r <= 16; r *= 2) {  // wavefronts whose pairs are merged
+        block_step<E>(k, lds, 64 * E * r - 1, (w & (r / 2)) != 0);
+#pragma unroll 1
+        for (uint32_t d = r / 4; d >= 1; d /= 2) block_step<E>(k, lds, 64 * E * d, (w & d) != 0);
+        clean<E, 32 * E>(k, lane);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (t * E + e < m) sink(t * E + e, k[e]);
+}
+
+// The places of the run at `own` of a list of m pairs: a pair's is its index in its run
+// plus the number of smaller ones in each other run, four of which are in LDS at a
+// time (8 bytes more every 16 pairs, or the search's strides would meet in one
+// bank).
+template <class Sink>
+__device__ __forceinline__ void rank_run(uint64_t* lds, const uint64_t* __restrict__ list, uint32_t m, uint32_t own,
+                                         Sink sink) {
+    const uint32_t t = threadIdx.x, mine = min(m - own, (uint32_t)kBinBlockKeys);
+    auto at = [&](uint32_t i) -> uint64_t& { return lds[i + (i >> 4)]; };
+    uint64_t k[2];
+    uint32_t rank[2];
+#pragma unroll
+    for (uint32_t e = 0; e < 2; ++e) {
+        rank[e] = 2 * t + e;
+        k[e] = rank[e] < mine ? list[own + rank[e]] : ~0ull;
+    }
+    for (uint32_t o = 0; o < m; o += kBinMergeKeys) {
+        const uint32_t here = min(m - o, (uint32_t)kBinMergeKeys);
+#pragma unroll
+        for (uint32_t e = 0; e < kBinMergeKeys / 1024; ++e)
+            if (1024 * e + t < here) at(1024 * e + t) = list[o + 1024 * e + t];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t v = 0; v < kBinMergeKeys; v += kBinBlockKeys)
+            if (v < here && o + v != own)
+                count_below(min(here - v, (uint32_t)kBinBlockKeys), k, rank, [&](uint32_t i) { return at(v + i); });
+        __syncthreads();
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < 2; ++e)
+        if (2 * t + e < mine) sink(rank[e], k[e]);
+}
+
+// The lists above kBinBlockKeys.  The first pass makes one of up to kBinFan sorted
+// runs: lists of up to kBinFanKeys are done with it, in keys and vals; of longer
+// ones it leaves runs of kBinFanKeys in merged, of which the last pass makes one.
+//
+// A workgroup takes a range of values of about kBinBlockKeys pairs, twice that where
+// there are more runs than workgroups (one to a CU): its ends are order statistics of samples, one every 256 pairs of each run (more from 4,096
+// samples on; at another offset in each run, so that runs of one profile do not have theirs in
+// the same places), its pairs are what each run holds between them, gathered and
+// sorted.  A range with more pairs than fit is halved until what is taken does,
+// and the rest of it follows: any runs come out sorted, if not as fast.  So a
+// pair costs a pass about one sort of 2,048, whatever the length of its list.  Lists of
+// up to kBinRankKeys, few runs, are cheaper by ranks.
+//
+// What bounds it: the steps of the two sorts (16 wavefronts, a barrier for each
+// exchange between them) and the latency of the search for the ends.  Whole sorts
+// in a grid of 3,225 tiles, radix form / ranks in every other run of a list, whose
+// cost is the square of its runs / this (us): one list of 30,000 83 / 86 / 54, of 100,000
+// 85 / 199 / 73, of 1M 157 / 1,752 / 159, of 5M 505 / - / 1,050; four lists of
+// 250,000 157 / 474 / 166.
+template <bool LAST>
+__global__ void __launch_bounds__(1024) bin_merge_kernel(const uint64_t* __restrict__ src,
+                                                        const uint32_t* __restrict__ ranges,
+                                                        const uint2* __restrict__ runs,
+                                                        const uint32_t* __restrict__ n_runs,
+                                                        uint64_t* __restrict__ merged, uint64_t* __restrict__ keys,
+                                                        uint32_t* __restrict__ vals) {
+    constexpr uint32_t LEN = LAST ? kBinFanKeys : kBinBlockKeys, LOG_LEN = __builtin_ctz(LEN);
+    static_assert((LEN & (LEN - 1)) == 0 && LEN >> 8 >= 1, "whole samples a run");
+    __shared__ uint64_t lds[kBinMergeKeys + kBinMergeKeys / 16];
+    __shared__ uint64_t cut[2];
+    __shared__ uint32_t pre[kBinFan], first[kBinFan], wsum[16];
+    const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6;
+    // exclusive prefix of v over the workgroup, and the total
+    auto scan = [&](uint32_t v, uint32_t& total) {
+        const uint32_t incl = wave_incl_scan(v, (int)lane);
+        __syncthreads();
+        if (lane == 63) wsum[w] = incl;
+        __syncthreads();
+        uint32_t before = incl - v;
+        total = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 16; ++q) {
+            before += q < w ? wsum[q] : 0u;
+            total += wsum[q];
+        }
+        return before;
+    };
+    const uint32_t units = *n_runs, wide = units > (uint32_t)kBinMaxBlocks ? 1u : 0u;
+    // a workgroup's runs: one a round, or two neighbours
+    for (uint32_t u = blockIdx.x << wide; u < units; u += wide && !(u & 1) ? 1 : (gridDim.x << wide) - wide) {
+        const uint32_t tile = runs[u].x, own = runs[u].y;
+        const uint32_t a = ranges[2 * tile], m = ranges[2 * tile + 1] - a;
+        // uniform, as all of the control flow below
+        if (LAST && m <= (uint32_t)kBinFanKeys) continue;
+        if (!LAST && m <= (uint32_t)kBinRankKeys) {
+            rank_run(lds, src + a, m, own, [&](uint32_t i, uint64_t k) { finish_pair(keys, vals, a + i, tile, k); });
+            continue;
+        }
+        if (own / kBinBlockKeys & wide) continue;
+        const uint32_t group = LAST ? 0u : own / kBinFanKeys * kBinFanKeys;
+        const uint32_t size = LAST ? m : min(m - group, (uint32_t)kBinFanKeys);
+        const uint32_t n = (size + LEN - 1) / LEN;
+        const uint64_t* list = src + a + group;
+        // this range's number and theirs, the samples, and those at its ends
+        const uint32_t range = kBinBlockKeys << wide, j = (own - group) / range, nb = (size + range - 1) / range;
+        uint32_t log_s = 8;
+        while (size > 4096u << log_s) ++log_s;
+        auto offset = [&](uint32_t r) { return (r * 0x9E3779B1u) >> (32 - log_s); };
+        const uint32_t log_per = LOG_LEN - log_s, tail = size - (n - 1) * LEN, o = offset(n - 1);
+        const uint32_t samples = ((n - 1) << log_per) + (tail > o ? ((tail - o - 1) >> log_s) + 1 : 0u);
+        const uint32_t c0 = (uint32_t)((uint64_t)j * samples / nb), c1 = (uint32_t)((uint64_t)(j + 1) * samples / nb);
+        auto sample = [&](uint32_t i) {
+            const uint32_t r = i >> log_per;
+            return list[r * LEN + ((i - (r << log_per)) << log_s) + offset(r)];
+        };
+        auto at_cut = [&](uint32_t i, uint64_t k) {
+            if (i == c0) cut[0] = k;
+            if (i == c1) cut[1] = k;
+        };
+        __syncthreads();  // the cuts of the range before are read
+        if (samples <= 1024) sort_wide<1>(lds, samples, sample, at_cut);
+        else if (samples <= 2048) sort_wide<2>(lds, samples, sample, at_cut);
+        else sort_wide<4>(lds, samples, sample, at_cut);
+        __syncthreads();
+        const uint64_t end = j + 1 < nb ? cut[1] : ~0ull;
+        uint64_t ends[2] = {j > 0 ? cut[0] : 0ull, end};
+        // thread r: the pairs of run r below the two ends
+        const uint32_t len = t < n ? min(size - t * LEN, LEN) : 0u;
+        const uint64_t* run = list + (t < n ? t : 0u) * LEN;
+        uint32_t below[2] = {0u, 0u};
+        count_below(len, ends, below, [&](uint32_t i) { return run[i]; });
+        uint32_t start;
+        scan(below[0], start);
+        for (;;) {
+            uint32_t count, before = scan(below[1] - below[0], count);
+            // pairs are distinct, so that 8,192 neighbouring values fit at the latest (if a
+            // caller's rectangles repeat a pair, the bounds below still end the loops)
+            while (count > (uint32_t)kBinMergeKeys && ends[1] - ends[0] > 1) {
+                ends[1] = ends[0] + (ends[1] - ends[0]) / 2;
+                const uint64_t half[1] = {ends[1]};
+                uint32_t b[1] = {0u};
+                count_below(len, half, b, [&](uint32_t i) { return run[i]; });
+                below[1] = b[0];
+                before = scan(below[1] - below[0], count);
+            }
+            if (t < n) {
+                pre[t] = before;
+                first[t] = t * LEN + below[0];
             }
             __syncthreads();
-            uint32_t lo[PER];
-#pragma unroll
-            for (int j = 0; j < PER; ++j) lo[j] = 0u;
-#pragma unroll
-            for (uint32_t step = kBinBlockKeys / 2; step >= 1; step >>= 1)
-#pragma unroll
-                for (int j = 0; j < PER; ++j)
-                    if (lds[lo[j] + step - 1] < k[j]) lo[j] += step;
-#pragma unroll
-            for (int j = 0; j < PER; ++j) rank[j] += lo[j] + (lds[lo[j]] < k[j] ? 1u : 0u);
+            auto get = [&](uint32_t i) {
+                uint32_t r = 0;  // the last run that starts at or before i
+                for (uint32_t q = 1u << (31 - __builtin_clz(n)); q >= 1; q >>= 1)
+                    if (r + q < n && pre[r + q] <= i) r += q;
+                return list[first[r] + (i - pre[r])];
+            };
+            auto put = [&](uint32_t i, uint64_t k) {
+                const uint32_t to = a + group + start + i;
+                if (!LAST && m > (uint32_t)kBinFanKeys) merged[to] = k;
+                else finish_pair(keys, vals, to, tile, k);
+            };
+            if (count <= 1024) sort_wide<1>(lds, count, get, put);
+            else if (count <= 2048) sort_wide<2>(lds, count, get, put);
+            else if (count <= 4096) sort_wide<4>(lds, count, get, put);
+            else sort_wide<8>(lds, min(count, (uint32_t)kBinMergeKeys), get, put);
+            if (ends[1] == end) break;
+            start += count;
+            ends[0] = ends[1];
+            ends[1] = end;
+            below[0] = below[1];
+            const uint64_t all[1] = {end};
+            uint32_t b[1] = {0u};
+            count_below(len, all, b, [&](uint32_t i) { return run[i]; });
+            below[1] = b[0];
         }
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (256u * j + t < mine) finish_pair(keys, vals, a + rank[j], tile, k[j]);
     }
 }
 
@@ -492,6 +658,7 @@ BinWs carve_bins(void* base, int64_t n, int64_t cap, int64_t tiles, size_t* byte
     w.totals = c.take<uint32_t>(tiles > 0 ? tiles : 1);
     w.runs = c.take<uint2>(bin_max_runs(cap));
     w.n_runs = c.take<uint32_t>(1);
+    w.merged = c.take<uint64_t>(cap > kBinFanKeys ? cap : 0);
     *bytes = c.total();
     return w;
 }
@@ -519,9 +686,12 @@ xgs_status bin_tile_sort(const xgs_projected* p, int64_t n, int tiles_x, int64_t
     const int longs = std::min(T, kBinLongBlocks);
     hipLaunchKernelGGL(bin_sort_kernel, dim3((unsigned)(longs + (T + 3) / 4)), dim3(256), 0, st, w.pairs, b->ranges,
                        b->tile_order, T, longs, w.runs, w.n_runs, b->keys, b->vals);
-    if (b->max_instances > kBinBlockKeys)
-        hipLaunchKernelGGL(bin_merge_kernel, dim3((unsigned)std::min<int64_t>(bin_max_runs(b->max_instances), 512)),
-                           dim3(256), 0, st, w.pairs, b->ranges, w.runs, w.n_runs, b->keys, b->vals);
+    auto merge = [&](auto kernel, const uint64_t* src) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(bin_max_runs(b->max_instances), kBinMergeBlocks)),
+                           dim3(1024), 0, st, src, b->ranges, w.runs, w.n_runs, w.merged, b->keys, b->vals);
+    };
+    if (b->max_instances > kBinBlockKeys) merge(bin_merge_kernel<false>, w.pairs);
+    if (b->max_instances > kBinFanKeys) merge(bin_merge_kernel<true>, w.merged);
     return check_launch("xgs_tile_sort bins");
 }
 

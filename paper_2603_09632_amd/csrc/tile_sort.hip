@@ -293,8 +293,9 @@ extern "C" xgs_status xgs_tile_sort_noalloc(const xgs_projected* p, const xgs_ca
     if (xgs_status s = validate_camera(cam)) return s;
     if (n < 0 || b->max_instances < 0)
         return fail(XGS_ERR_INVALID_ARG, "xgs_tile_sort_noalloc: negative size");
-    const Grid g = grid_of(*cam);
-    const size_t need = xgs_tile_sort_workspace(n, b->max_instances, g.tx * g.ty);
+    // what the radix form needs: xgs_tile_sort takes it where the binning form's does not fit
+    size_t need = 0;
+    carve_sort(nullptr, n, b->max_instances, &need);
     if (need > kSortScratchBytes)
         return fail(XGS_ERR_CAPACITY, "xgs_tile_sort_noalloc: n = " + std::to_string(n) + " and max_instances = " +
                                           std::to_string(b->max_instances) + " need " + std::to_string(need) +
