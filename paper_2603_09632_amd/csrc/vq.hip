@@ -28,7 +28,8 @@
 //     and rescored with the direct FP32 form sum (x - e)^2; the smallest wins
 //     (lowest index on ties).
 // The FP32 plain path (vq_fp32_kernel) forms the direct sum for the codewords that
-// a sweep in FP32 on the matrix cores leaves as candidates, by a bound on its error.
+// a sweep in FP32 on the matrix cores leaves as candidates, by a bound on its error;
+// few codewords or columns take it for every codeword (vq_fp32_tiles_kernel).
 //
 // Update: rows are grouped by codeword with the stable radix sort, each
 // codeword's rows are summed as pieces of at most 128 rows whose sums are
@@ -465,6 +466,110 @@ __global__ void __launch_bounds__(256, 2) vq_fp32_kernel(const float* __restrict
     const int64_t r0 = (int64_t)blockIdx.x * (32 * XT);
     if (D <= P_MAXD && vq_fp32_certified<XT, VEC>(lds, X, N, D, E, K, r0, idx, dist)) return;
     vq_fp32_direct<XT, VEC>(lds, X, N, D, E, K, r0, idx, dist);
+}
+
+// Few codewords or few columns: every codeword's direct form, 64 rows x 64 codewords
+// a tile, the columns in chunks of 32 through LDS; a thread owns 4 x 4
+// distances.  Neither a sweep of 256 codewords nor lists and candidates for them.
+// What bounds it: the latency of a chunk's loads and barriers (one of 76,800 x 32
+// on 64 codewords is all of it, 15 us; 46 in the certified form).
+constexpr int T_BM = 64, T_BN = 64, T_BD = 32;
+
+__global__ void __launch_bounds__(256) vq_fp32_tiles_kernel(const float* __restrict__ X, int64_t N, int D,
+                                                     const float* __restrict__ E, int K,
+                                                     int32_t* __restrict__ idx, float* __restrict__ dist) {
+    __shared__ float xs[T_BD][T_BM + 4];
+    __shared__ float es[T_BD][T_BN + 4];
+    const int t = threadIdx.x, tr = t >> 4, tc = t & 15;
+    const int64_t r0 = (int64_t)blockIdx.x * T_BM;
+    float bd[4];
+    int bi[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { bd[i] = INFINITY; bi[i] = 0x7FFFFFFF; }
+    for (int c0 = 0; c0 < K; c0 += T_BN) {
+        float acc[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+        for (int d0 = 0; d0 < D; d0 += T_BD) {
+            // 64 x 32 floats of X and of E: 8 per thread each
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int e = k * 256 + t, row = e >> 5, dd = e & 31;
+                const int64_t gr = r0 + row;
+                const int gc = c0 + row;
+                xs[dd][row] = (gr < N && d0 + dd < D) ? X[gr * D + d0 + dd] : 0.f;
+                es[dd][row] = (gc < K && d0 + dd < D) ? E[(size_t)gc * D + d0 + dd] : 0.f;
+            }
+            __syncthreads();
+#pragma unroll 8
+            for (int dd = 0; dd < T_BD; ++dd) {
+                const float4 xv = *reinterpret_cast<const float4*>(&xs[dd][tr * 4]);
+                const float4 ev = *reinterpret_cast<const float4*>(&es[dd][tc * 4]);
+                const float xa[4] = {xv.x, xv.y, xv.z, xv.w}, ea[4] = {ev.x, ev.y, ev.z, ev.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float df = xa[i] - ea[j];
+                        acc[i][j] += df * df;
+                    }
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = c0 + tc * 4 + j;
+            if (c < K)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (better(acc[i][j], c, bd[i], bi[i])) { bd[i] = acc[i][j]; bi[i] = c; }
+        }
+    }
+    // merge the 16 threads (consecutive lanes) that share a row group
+#pragma unroll
+    for (int k = 8; k >= 1; k >>= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float od = __shfl_xor(bd[i], k, 64);
+            const int oi = __shfl_xor(bi[i], k, 64);
+            if (better(od, oi, bd[i], bi[i])) { bd[i] = od; bi[i] = oi; }
+        }
+    if (tc == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t r = r0 + tr * 4 + i;
+            if (r < N) { idx[r] = bi[i]; dist[r] = bd[i]; }
+        }
+}
+
+// Whether the tiles are the faster form: times of both in one unit, for T64 and T256
+// tiles of 64 and 256 codewords and C chunks of 32 columns.  The two scale alike
+// only from 32,768 rows on, where the certified form takes 64 rows a workgroup; below,
+// its workgroups of 32 fill the card later.  Rows that are not whole aligned groups
+// of four cost the certified form scalar loads.  Measured, tiles / certified (us):
+//   5,000 rows   32 columns, 64 codewords 9 / 10, 128 14 / 11; 128 columns, 64: 23 / 17
+//   14,000       32, 64: 9 / 13, 128: 14 / 13; 128, 64: 23 / 22, 128: 43 / 23
+//   20,000       32, 64: 9 / 22, 192: 19 / 21, 256: 24 / 22; 384, 64: 88 / 77
+//   32,000       32, 64: 9 / 23, 256: 24 / 25; 128, 128: 42 / 43; 768, 64: 179 / 178
+//   76,800       32, 64: 15 / 46, 256: 48 / 48, 512: 90 / 73; 128, 64: 59 / 90, 128: 99 / 90,
+//                256: 191 / 92; 768, 64: 341 / 433, 256: 1,366 / 390
+static bool vq_fp32_by_tiles(int64_t N, int D, int K, bool vec) {
+    struct Cost {
+        int64_t rows;                          // up to
+        double tile;                           // tiles: per T64 C
+        double base, sweep, columns, ragged;   // certified: base + T256 (sweep + C columns)
+    };
+    static constexpr Cost costs[] = {{8192, 5.0, 7.0, 0.0, 2.0, 4.0},
+                                     {16384, 5.0, 7.0, 0.0, 3.0, 6.0},
+                                     {24576, 5.6, 6.5, 6.0, 5.0, 10.0},
+                                     {32767, 5.0, 13.5, 5.0, 5.5, 10.0},
+                                     {INT64_MAX, 11.0, 32.0, 8.0, 16.0, 28.0}};
+    const Cost* c = costs;
+    while (N > c->rows) ++c;
+    const double t64 = (K + 63) / 64, t256 = (K + 255) / 256, cols = (D + 31) / 32;
+    return c->tile * t64 * cols < c->base + t256 * (c->sweep + cols * (vec ? c->columns : c->ragged));
 }
 
 // -------------------------------------------------- BF16 MFMA + rescore
@@ -1928,6 +2033,11 @@ extern "C" xgs_status xgs_vq_assign(const float* X, int64_t N, int32_t D, const 
         // codewords 1,200 rows take 185 us by 32 and 305 by 64, 16,384 302 and 338, 32,768
         // 551 and 500, 76,800 1,410 and 1,324
         const bool wide = N >= 64 * 512, vec = D % 4 == 0 && aligned(X, 16) && aligned(E, 16);
+        if (vq_fp32_by_tiles(N, D, K, vec)) {
+            hipLaunchKernelGGL(vq_fp32_tiles_kernel, dim3((unsigned)((N + T_BM - 1) / T_BM)), dim3(256), 0,
+                               (hipStream_t)stream, X, N, D, E, K, idx, dist);
+            return check_launch("xgs_vq_assign fp32");
+        }
         const dim3 grid((unsigned)((N + (wide ? 63 : 31)) / (wide ? 64 : 32)));
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, X, N, D, E, K, idx, dist);
