@@ -355,7 +355,9 @@ __global__ void __launch_bounds__(256) sem_loss_kernel(const float* __restrict__
 // two workgroups a CU, so E's operands (L <= 16, where they fit) are asked for
 // before the targets and before the barriers: asked for at their use, eight waits
 // for L2 a block made 200 us of the 182.  Two reads and two decodes of every
-// target (the kernel above) took 302.
+// target (the kernel above) took 302.  More codes are bound by the products: the
+// whole call (us) with two reads and so, 32 codes 496 and 267, 64 codes 825 and 528
+// (from 513 columns on, 64 codes spill 32 registers a lane: 1,024 1,583 and 966).
 constexpr int SEM_REG_PIX = 32;
 constexpr int SEM_REG_TILES = 4;   // column tiles of a wavefront
 
@@ -426,8 +428,10 @@ __global__ void __launch_bounds__(64 * NW) sem_loss_regs_kernel(const float* __r
                                                         : f4u{0.f, 0.f, 0.f, 0.f};
             }
         };
-        // a wavefront without its last tile loads the last one there is, and leaves it unused
-        auto tile = [&](int i) { return min(q + NW * i, MT - 1); };
+        // a wavefront without its last tile loads the last one there is, and leaves it unused;
+        // where loads are not whole anyway, it loads none
+        auto tile = [&](int i) { return WHOLE ? min(q + NW * i, MT - 1) : q + NW * i; };
+        auto load = [&](int i) { return WHOLE || i == 0 || q + NW * i < MT; };
         float wb[2][KS];
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
@@ -439,10 +443,12 @@ __global__ void __launch_bounds__(64 * NW) sem_loss_regs_kernel(const float* __r
         float ea[HELD ? NT : 1][KS];
         if constexpr (HELD)
 #pragma unroll
-            for (int i = 0; i < NT; ++i) load_ea(tile(i), ea[i]);
+            for (int i = 0; i < NT; ++i)
+                if (load(i)) load_ea(tile(i), ea[i]);
         f2u b[NT][4];
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
+            if (!load(i)) break;
             const int d0 = 16 * tile(i);  // D % 4 == 0: a lane's four rows are all in or all out
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -490,7 +496,8 @@ __global__ void __launch_bounds__(64 * NW) sem_loss_regs_kernel(const float* __r
         f4u ec[HELD ? NT : 1][CT];
         if constexpr (HELD)
 #pragma unroll
-            for (int i = 0; i < NT; ++i) load_ec(tile(i), ec[i]);
+            for (int i = 0; i < NT; ++i)
+                if (load(i)) load_ec(tile(i), ec[i]);
         __syncthreads();
         if (q == (int)(blockIdx.x % NW)) {
             // one wavefront forms the pixels' coefficients, a pixel per lane (twice)
@@ -628,9 +635,25 @@ extern "C" xgs_status xgs_semantic_softmax_bwd(const float* w, const float* dw, 
 
 // Workgroups of the two forms: the one that holds its targets in registers takes
 // up to 64 column tiles (four a wavefront, 16 wavefronts), the other what is beyond,
-// and calls whose workspace holds only the other's partial losses.
+// calls whose workspace holds only the other's partial losses, and those below.
 static size_t sem_blocks(int64_t P, int pix) { return (size_t)((P + pix - 1) / pix); }
 constexpr int kSemRegsMaxD = 16 * 16 * SEM_REG_TILES;
+
+// Whether two reads of every target are the faster form: without a mask (which spares
+// the register form whole blocks), over so many pixels that both fill the card, where
+// the register form has wavefronts for many more tiles than there are; more so where
+// its loads are not whole (D % 16 != 0).  640 x 480, registers / two reads (us): 16
+// codes, D = 320 158 / 190, 516 364 / 303, 528 359 / 304, 592 384 / 343, 656 393 /
+// 382; 4 codes, 772 404 / 367, 900 447 / 426; 32 codes, 516 545 / 487, 644 618 / 606;
+// 64 codes, 260 521 / 449, 388 654 / 641.  16 codes, D = 516: at 256 x 256 67 / 75, at
+// 256 x 384 99 / 93.
+static bool sem_reads_twice(int64_t P, int L, int D, bool mask) {
+    if (mask || P < 98304) return false;
+    const int tiles = (D + 15) / 16;
+    const bool ragged = D % 16 != 0;
+    if (L <= 16) return tiles > 32 && tiles <= (ragged ? 56 : 40);
+    return ragged && ((tiles > 32 && tiles <= 36) || (L == 64 && tiles > 16 && tiles <= 18));
+}
 
 template <int L>
 static void launch_sem_regs(int64_t P, int D, const float* wmap, const float* E, const float* Gs, const uint8_t* V,
@@ -674,7 +697,7 @@ extern "C" xgs_status xgs_semantic_loss(const float* wmap, int32_t L, int32_t Hs
     if (!ws || ws_bytes < c.total()) return fail(XGS_ERR_CAPACITY, "xgs_semantic_loss: workspace too small");
     hipStream_t st = (hipStream_t)stream;
     if (V) hipLaunchKernelGGL(sem_count_kernel, dim3(kCountBlocks), dim3(1024), 0, st, V, P, counts);
-    const bool regs = D <= kSemRegsMaxD && ws_bytes >= regs_bytes;
+    const bool regs = D <= kSemRegsMaxD && ws_bytes >= regs_bytes && !sem_reads_twice(P, L, D, V != nullptr);
     const unsigned nb = (unsigned)sem_blocks(P, regs ? SEM_REG_PIX : SEM_PIX);
     if (regs) {
 #define XGS_SL(LL) launch_sem_regs<LL>(P, D, wmap, E, Gstar, V, lambda, counts, d_out, partial, st)
