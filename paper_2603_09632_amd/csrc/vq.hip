@@ -1968,11 +1968,12 @@ extern "C" xgs_status xgs_vq_candidates(int64_t N, int32_t D, int32_t K, void* w
 // Four rows per wavefront for many rows of at most 16 candidates that are
 // float4-aligned; one row per wavefront otherwise (the same bits).  The four-row form
 // shares its selection and sums between the rows, but is 30 KB of straight code
-// that few wavefronts run once.  Whole assignments by fours and by ones (us): 1,200 x
-// 768 on 1,024 53 and 39, 33,000 x 64 84 and 79, 50,000 x 128 117 and 113, 100,000 x
-// 128 191 and 196, 200,000 x 256 391 and 402; long rows hide more: 100,000 x 384 265
-// and 253, 200,000 x 768 751 and 732.
-static bool vq_few_rows(int64_t N, int D) { return N <= (D >= 384 ? 262144 : 65536); }
+// that few wavefronts run once; long rows hide more of that.  Whole assignments by
+// fours and by ones (us), plain: 1,200 x 768 on 1,024 53 and 39; on 256, 40,000 x 32
+// 63 and 59, 50,000 69 and 68, 65,536 78 and 81; 65,536 x 256 93 and 90, 100,000 x 128
+// on 1,024 191 and 196; 100,000 x 384 265 and 253, 200,000 x 768 751 and 732.  With
+// confidence on 256: 40,000 x 32 68 and 68, 50,000 74 and 77, 65,536 84 and 92.
+static bool vq_few_rows(int64_t N, int D) { return N <= (D >= 384 ? 262144 : D >= 256 ? 65536 : 45056); }
 
 template <bool CONF>
 static void launch_rescore(const float* X, int64_t N, int D, const float* E, int K, const int2* cand, int parts,
