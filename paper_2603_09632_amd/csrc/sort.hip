@@ -21,23 +21,39 @@ xgs_status fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t stream) {
 }
 
 // Zero fill of up to four ranges in one launch (blockIdx.y picks the range):
-// 16-byte stores for the aligned body, 4-byte stores for the ends.
-__global__ void zero_ranges_kernel(ZeroRanges r) {
+// 16-byte stores for the aligned body, 4-byte stores for the ends.  Bound by the
+// stores' rate: four a thread, 64 + 16 MB of a million Gaussians 11.5 us, one a
+// thread 13.7.
+constexpr int kZeroStores = 4;
+
+__global__ void __launch_bounds__(256) zero_ranges_kernel(ZeroRanges r) {
+    constexpr int U = kZeroStores;
     uint32_t* p = r.p[blockIdx.y];
     const int64_t n = r.n[blockIdx.y];
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t u0 = (int64_t)blockIdx.x * blockDim.x * U + threadIdx.x;
     if (r.seen && (int)blockIdx.y == r.seen_k) {  // uniform
         uint4* rows = reinterpret_cast<uint4*>(p);
-        for (int64_t i = t0; i < n / 4; i += stride)
-            if (r.seen[i / (ZeroRanges::kRow / 4)] > 0) rows[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int64_t i = u0; i < n / 4; i += stride * U) {
+            bool seen[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                seen[u] = i + 256 * u < n / 4 && r.seen[(i + 256 * u) / (ZeroRanges::kRow / 4)] > 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (seen[u]) rows[i + 256 * u] = make_uint4(0u, 0u, 0u, 0u);
+        }
         return;
     }
     const int64_t head = (int64_t)(((16 - ((uintptr_t)p & 15)) & 15) / 4);  // words before 16-byte alignment
     const int64_t h = head < n ? head : n;
     const int64_t nv = (n - h) / 4;
     uint4* pv = reinterpret_cast<uint4*>(p + h);
-    for (int64_t i = t0; i < nv; i += stride) pv[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t i = u0; i < nv; i += stride * U)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + 256 * u < nv) pv[i + 256 * u] = make_uint4(0u, 0u, 0u, 0u);
     const int64_t tail0 = h + 4 * nv;
     for (int64_t i = t0; i < h + (n - tail0); i += stride) p[i < h ? i : tail0 + (i - h)] = 0u;
 }
@@ -46,7 +62,7 @@ xgs_status zero_ranges(const ZeroRanges& r, hipStream_t stream) {
     int64_t most = 0;
     for (int j = 0; j < r.k; ++j) most = r.n[j] > most ? r.n[j] : most;
     if (r.k <= 0 || most <= 0) return XGS_OK;
-    int64_t blocks = (most / 4 + 255) / 256;
+    int64_t blocks = (most / 4 + 256 * kZeroStores - 1) / (256 * kZeroStores);
     if (blocks > 16384) blocks = 16384;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(zero_ranges_kernel, dim3((unsigned)blocks, (unsigned)r.k), dim3(256), 0, stream, r);
