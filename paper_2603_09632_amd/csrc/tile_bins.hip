@@ -628,9 +628,11 @@ __global__ void __launch_bounds__(1024) bin_merge_kernel(const uint64_t* __restr
                     if (r + q < n && pre[r + q] <= i) r += q;
                 return list[first[r] + (i - pre[r])];
             };
+            const bool final = LAST || m <= (uint32_t)kBinFanKeys;
+            const uint32_t to0 = a + group + start;
             auto put = [&](uint32_t i, uint64_t k) {
-                const uint32_t to = a + group + start + i;
-                if (!LAST && m > (uint32_t)kBinFanKeys) merged[to] = k;
+                const uint32_t to = to0 + i;
+                if (!final) merged[to] = k;
                 else finish_pair(keys, vals, to, tile, k);
             };
             if (count <= 1024) sort_wide<1>(lds, count, get, put);
