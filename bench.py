@@ -270,7 +270,7 @@ def main():
         result["mapping_scale"] = mapping_scale(xgs, synth, dev)
         result["semantic_phase"] = semantic_phase(xgs, synth, dev, G)
         result["tracking_and_targets"] = tracking_and_targets(xgs, g, p, b, cams[args.warmup + args.steps - 1], out,
-                                                              fT, nl, d_out, grads, bwd_ws, dev)
+                                                              fT, nl, d_out, bwd_ws, dev)
 
     if not args.no_serve:
         del X, Xh, G
@@ -303,9 +303,12 @@ def compositing_work(xgs, g, p, b, cam, out, fT, nl, c_sem, m_inst, fwd_ms, bwd_
     instance reads again, per instance one gradient row (2 + 3 + 1 + 3 + 1 +
     c_sem floats), per pixel d_out, final_T and n_last, and per Gaussian the
     projection backward (11 parameter and 3 + 3 + 4 + 1 + 3 + c_sem gradient
-    floats).  ALU: E (20 + C) FP32 lane operations forward and E (35 + 2 C)
-    backward (recompute alpha, recover T, g.c, d alpha, the chain to conic,
-    mean and opacity, w g), against VALU_PEAK_TOPS."""
+    floats).  Vector operations: 20 E FP32 lane operations forward (alpha, T, the
+    weight) and 35 E backward (recompute alpha, recover T, d alpha, the sums for
+    conic, mean and opacity), against VALU_PEAK_TOPS.  Matrix operations: the
+    channel sums, 2 E C flop forward and 4 E C backward (g.c and w g), against
+    FP32_PEAK_TFLOPS.  The kernels skip the splats that cannot reach a
+    quadrant of 8 x 8 pixels, which E counts."""
     import torch
     xgs.xgs_render_fwd(g, p, b, cam, out=out, final_T=fT, n_last=nl)
     _, _, ty, tx = xgs.grid_dims(cam)
@@ -323,30 +326,34 @@ def compositing_work(xgs, g, p, b, cam, out, fT, nl, c_sem, m_inst, fwd_ms, bwd_
     fwd_bytes = m_inst * inst_b + hs * ws * 4 * (C + 2)
     bwd_bytes = (m_inst * (inst_b + 4 * (10 + c_sem)) + hs * ws * 4 * (C + 2)
                  + n * 4 * (11 + 14 + c_sem))
-    fwd_ops, bwd_ops = E * (20 + C), E * (35 + 2 * C)
+    fwd_ops, bwd_ops = 20 * E, 35 * E
+    fwd_flop, bwd_flop = 2 * E * C, 4 * E * C
 
-    def roof(kernel, nbytes, ops, t_ms, what):
-        gbs = nbytes / (t_ms * 1e-3) / 1e9
-        tops = ops / (t_ms * 1e-3) / 1e12
-        hbm, alu = gbs / HBM_PEAK_GBS, tops / VALU_PEAK_TOPS
-        return {"kernel": kernel, "bound": "hbm" if hbm >= alu else "alu",
-                "achieved": round(gbs, 1) if hbm >= alu else round(tops, 2),
-                "peak": HBM_PEAK_GBS if hbm >= alu else round(VALU_PEAK_TOPS, 2),
-                "unit": "GB/s" if hbm >= alu else "Tops/s", "frac": round(max(hbm, alu), 4),
-                "hbm_GBps": round(gbs, 1), "hbm_frac": round(hbm, 4), "alu_Tops": round(tops, 2),
-                "alu_frac": round(alu, 4), "traffic": traffic_for(kernel + "<32", SRC[kernel], nbytes),
+    def roof(kernel, nbytes, ops, flop, t_ms, what):
+        rate = lambda x, unit: x / (t_ms * 1e-3) / unit
+        parts = {"hbm": (rate(nbytes, 1e9), HBM_PEAK_GBS, "GB/s"), "alu": (rate(ops, 1e12), VALU_PEAK_TOPS, "Tops/s"),
+                 "mfma": (rate(flop, 1e12), FP32_PEAK_TFLOPS, "TFLOP/s")}
+        bound = max(parts, key=lambda k: parts[k][0] / parts[k][1])
+        got, peak, unit = parts[bound]
+        frac = {k: round(v[0] / v[1], 4) for k, v in parts.items()}
+        return {"kernel": kernel, "bound": bound, "achieved": round(got, 2), "peak": round(peak, 2), "unit": unit,
+                "frac": frac[bound], "hbm_GBps": round(parts["hbm"][0], 1), "hbm_frac": frac["hbm"],
+                "alu_Tops": round(parts["alu"][0], 2), "alu_frac": frac["alu"],
+                "mfma_TFLOPs": round(parts["mfma"][0], 2), "mfma_frac": frac["mfma"], "traffic": traffic_for(kernel + "<32", SRC[kernel], nbytes),
                 "algorithmic": what, "ms": t_ms}
 
     return {
         "instances_M": m_inst, "evaluations_E": E, "evaluations_E_list": E_list,
         "mean_walk_per_pixel": round(E / (hs * ws), 1),
         "fwd_bytes": fwd_bytes, "bwd_bytes": bwd_bytes, "fwd_ops": fwd_ops, "bwd_ops": bwd_ops,
+        "fwd_flop": fwd_flop, "bwd_flop": bwd_flop,
         "valu_peak_Tops": round(VALU_PEAK_TOPS, 2),
-        "roofline_fwd": roof("render_fwd_mfma_kernel", fwd_bytes, fwd_ops, fwd_ms,
-                             f"M*{inst_b} + px*4*(C+2) = {fwd_bytes:.3e} B; E*(20+C) = {fwd_ops:.3e} ops"),
-        "roofline_bwd": roof("render_bwd_mfma_kernel", bwd_bytes, bwd_ops, bwd_ms,
+        "roofline_fwd": roof("render_fwd_mfma_kernel", fwd_bytes, fwd_ops, fwd_flop, fwd_ms,
+                             f"M*{inst_b} + px*4*(C+2) = {fwd_bytes:.3e} B; 20*E = {fwd_ops:.3e} ops; "
+                             f"2*E*C = {fwd_flop:.3e} flop"),
+        "roofline_bwd": roof("render_bwd_mfma_kernel", bwd_bytes, bwd_ops, bwd_flop, bwd_ms,
                              f"M*({inst_b}+4*(10+c_sem)) + px*4*(C+2) + N*4*(25+c_sem) = {bwd_bytes:.3e} B; "
-                             f"E*(35+2C) = {bwd_ops:.3e} ops; time of the whole xgs_render_bwd call "
+                             f"35*E = {bwd_ops:.3e} ops; 4*E*C = {bwd_flop:.3e} flop; time of the whole xgs_render_bwd call "
                              "(gradient fill, pixel kernel, projection backward)"),
     }
 
@@ -464,9 +471,10 @@ def semantic_phase(xgs, synth, dev, G, reps: int = 10):
             "decode_loss_bytes": loss_bytes}
 
 
-def tracking_and_targets(xgs, g, p, b, cam, out, fT, nl, d_out, grads, bwd_ws, dev, reps: int = 10):
-    """Tracking pieces on the 1M-Gaussian 1200x680 frame (loss -> backward ->
-    pose gradient), occluder pruning of the 1M Gaussians against a depth map,
+def tracking_and_targets(xgs, g, p, b, cam, out, fT, nl, d_out, bwd_ws, dev, reps: int = 10):
+    """Tracking pieces on the 1M-Gaussian 1200x680 frame (loss over colour and
+    depth -> backward of the pose's sums -> pose gradient, as tracking_step
+    runs them), occluder pruning of the 1M Gaussians against a depth map,
     and region-indexed targets at 640x480 (D = 512, 100 regions)."""
     import torch
     log("tracking, occluder pruning, region targets")
@@ -493,9 +501,9 @@ def tracking_and_targets(xgs, g, p, b, cam, out, fT, nl, d_out, grads, bwd_ws, d
 
     def run(evs):
         evs[0].record(stream)
-        xgs.xgs_tracking_loss(out, image, depth, 0.05, d_out=d_out, loss=loss, workspace=tws)
+        xgs.xgs_tracking_loss(out[:4], image, depth, 0.05, d_out=d_out[:4], loss=loss, workspace=tws)
         evs[1].record(stream)
-        xgs.xgs_render_bwd(g, p, b, cam, d_out, fT, nl, grads=grads, workspace=bwd_ws)
+        xgs.xgs_render_bwd(g, p, b, cam, d_out[:4], fT, nl, flags=xgs.BWD_POSE, workspace=bwd_ws)
         evs[2].record(stream)
         xgs.xgs_pose_grad(g, p, cam, bwd_ws, d_pose=d_pose)
         evs[3].record(stream)
