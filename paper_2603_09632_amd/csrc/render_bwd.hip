@@ -86,6 +86,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
     constexpr int CHP = (CH + 3) / 4 * 4;           // LDS row stride (float4 rows)
     constexpr int COLS = POSE ? 0 : GEO ? CH : CS;  // columns of W^T G: features, then colour and depth
     constexpr int NT = (COLS + 15) / 16;
+    static_assert(!GEO || CS % 16 <= 12, "colour and depth are in one tile");
     constexpr int ROW = 20;                         // LDS row of a pixel: 16 splats, float4-aligned, banks spread
     __shared__ __align__(16) float wl[64 * ROW];    // g.c of (pixel, splat), then its weight
     __shared__ Ring ring;

@@ -96,6 +96,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS > 32
     // lane-constant source and stride, so that its loads do not branch.
     const int fstr = EXACT ? CS : csem;
     constexpr int MIX = OWN4 ? NT : CS / 16;  // that tile
+    static_assert(CS % 16 <= 12, "colour and depth fit the features' last tile: it is the last");
     const int jm = 16 * MIX + (lane & 15);
     const bool mfeat = jm < CS, muse = jm < COLS && (EXACT || jm < csem || jm >= CS);
     const float* const msrc = !muse ? reinterpret_cast<const float*>(splat)
@@ -155,9 +156,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS > 32
                 for (int nt = 0; nt < NT; ++nt) {
                     const int j = 16 * nt + (lane & 15);
                     if (nt == MIX) b[kk][nt] = msrc[(size_t)gs * mstr];
-                    else if (nt < MIX) b[kk][nt] = *at_row<OFF>(features, gs, fstr, EXACT ? j : min(j, csem - 1));
-                    else b[kk][nt] = j < CS + 3 ? colors[3 * (size_t)gs + (j - CS)]
-                                     : reinterpret_cast<const float*>(splat)[8 * (size_t)gs + 6];
+                    else b[kk][nt] = *at_row<OFF>(features, gs, fstr, EXACT ? j : min(j, csem - 1));
                 }
             }
             float w[16];
