@@ -1,7 +1,7 @@
 // a2, tile sort by binning: the (tile, Gaussian) instances are counted per
 // tile, dropped into their tile's segment and sorted there by (depth,
 // Gaussian).  Five launches: count, scan, scatter, sort, and a merge that only
-// lists above 2,048 instances need (a second one above 1M).
+// lists above 2,048 instances need (a second one above 2M).
 //
 // A radix sort over the 41-46 key bits moves every pair five or six times and
 // takes 19 dependent launches, whose latency alone was most of its time.  The
@@ -526,11 +526,11 @@ __device__ __forceinline__ void rank_run(uint64_t* lds, const uint64_t* __restri
 // up to kBinRankKeys, few runs, are cheaper by ranks.
 //
 // What bounds it: the steps of the two sorts (16 wavefronts, a barrier for each
-// exchange between them) and the latency of the search for the ends.  Whole sorts
-// in a grid of 3,225 tiles, radix form / ranks in every other run of a list, whose
-// cost is the square of its runs / this (us): one list of 30,000 83 / 86 / 54, of 100,000
-// 85 / 199 / 73, of 1M 157 / 1,752 / 159, of 5M 505 / - / 1,050; four lists of
-// 250,000 157 / 474 / 166.
+// exchange between them) and the scattered loads of the search for the ends.
+// Whole sorts in a grid of 3,225 tiles, radix form / ranks in every other run of a
+// list, whose cost is the square of its runs / this (us): one list of 30,000 83 / 86
+// / 61, of 100,000 85 / 199 / 70, of 1M 157 / 1,752 / 158, of 2M 229 / - / 355, of 5M
+// 505 / - / 1,080; four lists of 250,000 157 / 474 / 162.
 template <bool LAST>
 __global__ void __launch_bounds__(1024) bin_merge_kernel(const uint64_t* __restrict__ src,
                                                         const uint32_t* __restrict__ ranges,
