@@ -19,8 +19,8 @@ constexpr int kBinMaxTiles = 16384;
 constexpr int kBinWaveKeys = 256;
 constexpr int kBinBlockKeys = 2048;
 // Runs that the first pass of the merge makes one, and so the longest lists that
-// need no other (a list has at most 8,193 x 16,384 pairs, 65 of them); pairs that a workgroup of the merge sorts in LDS, and those
-// workgroups (one fills a CU).
+// need no other (a list has at most 8,193 x 16,384 pairs, 65 of them); pairs that a
+// workgroup of the merge sorts in LDS, and those workgroups (one fills a CU).
 constexpr int kBinFan = 1024;
 constexpr int kBinFanKeys = kBinFan * kBinBlockKeys;
 constexpr int kBinMergeKeys = 8192;
