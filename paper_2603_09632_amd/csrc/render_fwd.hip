@@ -30,9 +30,10 @@ namespace xgs {
 // walk and used after it.  The accumulators hold the wave's output block until
 // the end.
 //
-// What bounds it: the vector and matrix instructions of the walk (their cycles
-// add up to 70% of a SIMD's at 4 wavefronts, 3 above 32 channels) and, where few
-// lists are long, the longest list's walk.  Measured with masks in scalar
+// What bounds it: the vector and matrix instructions of the walk (on the 1M frame
+// below their cycles are 62% and 31% of a SIMD's, and they hardly overlap, at 4
+// wavefronts, 3 above 32 channels) and, where few lists are long, the longest
+// list's walk.  Measured with masks in scalar
 // registers, colour and depth in a tile of 16 columns, one store a pixel and
 // channel, and as it is (four pixels of a row are one store): 1M Gaussians, 1200
 // x 680, 32 features 155-191 -> 103-143 us by the pose; 300k, 640 x 480, 16
