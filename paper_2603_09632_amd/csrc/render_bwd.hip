@@ -297,8 +297,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CS <= 1
                 w[u] = b * T;
                 if constexpr (GEO) {
                     const float s = ok[u] ? sd[u >> 2][u & 3] : 0.f;  // a colour may be infinite
-                    // a pair without a part in the pixel has h = 0 also where S is not finite
-                    const float h = ok[u] && al[u] < kAlphaMax ? b * (T * s - S) : 0.f;
+                    // 0 < alpha < the clamp, in one comparison of bits: a pair without a part in
+                    // the pixel has h = 0 also where S is not finite
+                    const bool live = __float_as_uint(al[u]) - 1u < __float_as_uint(kAlphaMax) - 1u;
+                    const float h = live ? b * (T * s - S) : 0.f;
                     S += w[u] * s;
                     a[V * u] = h;
                     a[V * u + 1] = h * dy[u];

@@ -162,7 +162,8 @@ __global__ void __launch_bounds__(kBinThreads) bin_scatter_kernel(
     uint32_t* __restrict__ ranges, int64_t* __restrict__ count, int32_t* __restrict__ status,
     uint32_t* __restrict__ order, uint2* __restrict__ runs, uint32_t* __restrict__ n_runs) {
     extern __shared__ uint32_t pos[];
-    __shared__ uint64_t wtot[kBinWaves];
+    __shared__ uint32_t wtot[kBinWaves];
+    __shared__ float wabout[kBinWaves];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     // wavefront w scans its run of tiles 64 at a time, then adds the runs
     // before it; every total and offset is loaded before the first is used
@@ -183,8 +184,9 @@ __global__ void __launch_bounds__(kBinThreads) bin_scatter_kernel(
         off[j] = k < hi ? row[k] : 0u;
     }
     // The positions fit 32 bits wherever they are used, but the total that says
-    // so may not: 64 tiles of 2^26 instances each make 2^32.
-    uint64_t sum = 0;
+    // so may not (64 tiles of 2^26 instances each make 2^32): a sum in floats, right
+    // to some millionths, tells whether it does.
+    float about = 0.f;
     uint32_t first[STEPS], carry = 0;
 #pragma unroll
     for (int j = 0; j < STEPS; ++j) {
@@ -192,19 +194,25 @@ __global__ void __launch_bounds__(kBinThreads) bin_scatter_kernel(
         const uint32_t incl = wave_incl_scan(tv[j], lane);
         first[j] = carry + incl - tv[j];
         carry += __builtin_amdgcn_readlane(incl, 63);
-        sum += tv[j];
+        about += (float)tv[j];
     }
-    sum = wave_sum_u64(sum, lane);
-    if (lane == 0) wtot[w] = sum;
+    about = wave_sum(about);
+    if (lane == 0) {
+        wtot[w] = carry;
+        wabout[w] = about;
+    }
     __syncthreads();
-    uint64_t base = 0, total = 0;
+    uint32_t base = 0, total = 0;
+    about = 0.f;
 #pragma unroll
     for (int k = 0; k < kBinWaves; ++k) {
-        const uint64_t x = wtot[k];
-        base += k < w ? x : 0ull;
+        const uint32_t x = wtot[k];
+        base += k < w ? x : 0u;
         total += x;
+        about += wabout[k];
     }
-    const bool over = total > (uint64_t)cap;
+    // (the capacity is below 2^28)
+    const bool over = about > 0x1p31f || total > (uint32_t)cap;
     if (last) {
         // the runs of the lists above kBinBlockKeys
         uint32_t nr[STEPS], mine = 0;
@@ -220,8 +228,8 @@ __global__ void __launch_bounds__(kBinThreads) bin_scatter_kernel(
         uint32_t to = incl - mine, all = 0;
 #pragma unroll
         for (int k = 0; k < kBinWaves; ++k) {
-            to += k < w ? (uint32_t)wtot[k] : 0u;
-            all += (uint32_t)wtot[k];
+            to += k < w ? wtot[k] : 0u;
+            all += wtot[k];
         }
 #pragma unroll
         for (int j = 0; j < STEPS; ++j)
@@ -236,7 +244,7 @@ __global__ void __launch_bounds__(kBinThreads) bin_scatter_kernel(
         const int k = lo + 64 * j + lane;
         if (lo + 64 * j >= hi) break;
         if (k >= hi) continue;
-        const uint32_t at0 = first[j] + (uint32_t)base;
+        const uint32_t at0 = first[j] + base;
         if (blockIdx.x == 0) {
             const uint32_t len = over ? 0u : tv[j];
             ranges[2 * k] = len ? at0 : 0u;

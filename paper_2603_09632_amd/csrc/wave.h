@@ -9,8 +9,6 @@
 // Each partner map is an involution; the six generators (32, 16, 8, 7, 3, 1)
 // span all 64 lanes, so six steps combine every lane exactly once.
 #pragma once
-#include <type_traits>
-
 #include "common.h"
 
 namespace xgs {
@@ -63,22 +61,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     v += xlane_dpp<4>(v);
     v += xlane_dpp<2>(v);
     v += xlane_dpp<1>(v);
-    return v;
-}
-
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v, int lane) {
-    auto add = [&](auto k) {
-        constexpr int K = decltype(k)::value;
-        const uint32_t lo = (uint32_t)xlane_partner<K>((int)(uint32_t)v, lane);
-        const uint32_t hi = (uint32_t)xlane_partner<K>((int)(uint32_t)(v >> 32), lane);
-        v += (uint64_t)hi << 32 | lo;
-    };
-    add(std::integral_constant<int, 32>{});
-    add(std::integral_constant<int, 16>{});
-    add(std::integral_constant<int, 8>{});
-    add(std::integral_constant<int, 4>{});
-    add(std::integral_constant<int, 2>{});
-    add(std::integral_constant<int, 1>{});
     return v;
 }
 
